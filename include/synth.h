@@ -440,17 +440,18 @@ int synth_scale_rows(const float* g, const double* s, int64_t rows, int64_t cols
  * (V-statistic) estimate over all pairs, self-pairs included,
  *   MMD(X, Y) = 2 S(X, Y) / (n m) - S(X, X) / n^2 - S(Y, Y) / m^2,
  *   S(A, B)   = sum_{i, j} sum_k |A[i][k] - B[j][k]|.
- * Each sum accumulates a pair's distance in float32 over runs of 256
- * dimensions and everything else in float64, in a fixed order, so results
- * are bitwise reproducible.
+ * Sets of up to 2048 sounds are summed in float64 from each dimension's
+ * sorted values; beyond that (and where one set is much the smaller) a pair's
+ * distance is accumulated in float32 over runs of 256 dimensions and
+ * everything else in float64.  Both in a fixed order, so results are bitwise
+ * reproducible.
  * ------------------------------------------------------------------------- */
 
 /* Bytes of device workspace synth_l1_pair_sum needs for sets of n and m
  * embeddings of dim floats (0 for an empty set or n, m above 2^17). */
 size_t synth_l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim);
 
-/* Bytes of device workspace synth_mmd_l1 needs: the largest of the three
- * pair sums' (n, m), (n, n), (m, m). */
+/* Bytes of device workspace synth_mmd_l1 needs. */
 size_t synth_mmd_l1_workspace(int64_t n, int64_t m, int64_t dim);
 
 /* out[0] = S(A, B) (dev float64) for A dev float32 [n][dim] (row stride lda
@@ -464,7 +465,7 @@ int synth_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, in
 
 /* out[0..3] = {MMD(X, Y), S(X, Y), S(X, X), S(Y, Y)} (dev float64 [4]) for X
  * dev float32 [n][dim], Y dev float32 [m][dim] (dense rows), 1 <= n, m <=
- * 2^17.  MMD(X, X) is exactly 0: S(X, X) is computed as S(X, Y) would be for
+ * 2^17.  MMD(X, X) is exactly 0: the terms of S(X, X) are those of S(X, Y) for
  * Y = X.  workspace >= synth_mmd_l1_workspace(n, m, dim) bytes.  Errors as
  * synth_l1_pair_sum. */
 int synth_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,

@@ -740,11 +740,8 @@ size_t synth_l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
 }
 
 size_t synth_mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
-  size_t need = synth_l1_pair_sum_workspace(n, m, dim);
-  const size_t xx = synth_l1_pair_sum_workspace(n, n, dim);
-  const size_t yy = synth_l1_pair_sum_workspace(m, m, dim);
-  need = xx > need ? xx : need;
-  return yy > need ? yy : need;
+  if (n <= 0 || m <= 0 || dim < 0 || n > kMaxSet || m > kMaxSet) return 0;
+  return synth::mmd_l1_workspace(n, m, dim);
 }
 
 int synth_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
@@ -766,14 +763,8 @@ int synth_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t d
   if (dim > 0 && (!X || !Y)) return SYNTH_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 7)) return SYNTH_EINVAL;
   if (workspace_bytes < synth_mmd_l1_workspace(n, m, dim)) return SYNTH_ENOMEM;
-  const hipStream_t s = (hipStream_t)stream;
-  double* ws = (double*)workspace;
-  // the three sums reuse the workspace in stream order
-  hipError_t e = synth::launch_l1_pair_sum(X, dim, n, Y, dim, m, dim, ws, out + 1, s);
-  if (e == hipSuccess) e = synth::launch_l1_pair_sum(X, dim, n, X, dim, n, dim, ws, out + 2, s);
-  if (e == hipSuccess) e = synth::launch_l1_pair_sum(Y, dim, m, Y, dim, m, dim, ws, out + 3, s);
-  if (e == hipSuccess) e = synth::launch_mmd_combine(out, n, m, s);
-  return to_status(e);
+  return to_status(synth::launch_mmd_l1(X, n, Y, m, dim, (double*)workspace, out,
+                                        (hipStream_t)stream));
 }
 
 int64_t synth_vcf_state_chunks(int64_t max_samples, int period) {

@@ -5,6 +5,9 @@
 //   S(A, B) = sum_{i < n, j < m} sum_k |A[i][k] - B[j][k]|
 //   MMD(X, Y) = 2 S(X, Y) / (n m) - S(X, X) / n^2 - S(Y, Y) / m^2.
 //
+// Two ways: by sorting each dimension's values (sets of up to 2048 sounds,
+// sorted_pair_sum_kernel below), and over all pairs (l1_pair_sum_kernel):
+//
 // Workgroups of 256 threads take tiles of 64 x 64 pairs and one share of
 // the embedding dimension (whole runs of 256 dimensions, so tiles x shares
 // fills the chip even for sets of a few hundred sounds).  The dimension is
@@ -170,15 +173,394 @@ __global__ void mmd_combine_kernel(double* out, int64_t n, int64_t m) {
   }
 }
 
-}  // namespace
+// ---------------------------------------------------------------------------
+// Pair sums by sorting.  S(A, B) needs no single pair's distance, only the sum
+// over all pairs, and that follows from each dimension's values in ascending
+// order: the gap between neighbours k and k + 1 of the merged values of A and
+// B counts once for every pair it separates, so with a and b values of A and
+// B up to k
+//   S(A, B) = sum_k gap_k (a (m - b) + b (n - a)),
+//   S(A, A) = sum_k gap_k 2 a (n - a),   S(B, B) = sum_k gap_k 2 b (m - b):
+// (n + m) log^2(n + m) operations per dimension instead of n m + n n + m m,
+// all terms non-negative and all sums float64 (the all-pairs kernel adds a
+// distance in float32 over runs of 256 dimensions; against float64 the three
+// sums of 1000 x 1000 x 8192 log-mel-like features were 4.1e-8 off and are
+// 1e-15 off).  For B = A every term of the three sums is the same number, so
+// MMD(X, X) is exactly 0 here too.
+//
+// One wavefront sorts one dimension in registers: lanes 0-31 hold A, lanes
+// 32-63 hold B, R values each (32 R >= max(n, m), the rest padded with the
+// largest float).  Bitonic sort in the form whose merges begin with a mirrored
+// exchange, so every comparison is ascending: distances below R are register
+// pairs (one min and one max), lane distances are DPP moves and one median
+// with +-infinity per value.  The last merge, of A with B, has to remember
+// where a value came from: it runs on the values as float64, whose 29 spare
+// mantissa bits hold the mark.  A workgroup of C wavefronts stages C
+// neighbouring dimensions of all rows through LDS (C floats = 64 bytes of a
+// row, padded to C + 1: the lanes of a wavefront read 32 rows of one dimension
+// from distinct banks).
+//
+// Bound by VALU issue at R = 32 (about 4900 instructions per wavefront and
+// dimension, four wavefronts per SIMD).  MMD of 1000 x 1000 sounds of 8192
+// features: 1.31 ms (three all-pairs launches) -> 0.08 ms.
+// ---------------------------------------------------------------------------
+constexpr int kSortFlagNan = 1, kSortFlagPos = 2, kSortFlagNeg = 4;
 
-size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
-  const PairPlan p = pair_plan(n, m, dim);
-  return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+__device__ __forceinline__ int sort_key(float x) {      // monotone int of a float
+  const int i = __float_as_int(x);
+  return i ^ ((i >> 31) & 0x7FFFFFFF);
+}
+__device__ __forceinline__ float sort_value(int k) {    // and back
+  return __int_as_float(k ^ ((k >> 31) & 0x7FFFFFFF));
 }
 
-hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
-                              int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
+__device__ __forceinline__ int med3_i32(int x, int y, int z) {
+  // z = INT_MAX gives max(x, y), INT_MIN gives min(x, y): the compiler folds
+  // this shape to one v_med3_i32
+  const int lo = x < y ? x : y, hi = x < y ? y : x;
+  const int c = hi < z ? hi : z;
+  return lo > c ? lo : c;
+}
+
+// Value of lane (lane ^ D) for D = 1, 2, 4, 8, 16 and of the mirrored lane of
+// a group of 2, 4, 8, 16, 32, 64 lanes.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
+}
+template <int D>
+__device__ __forceinline__ int lane_xor(int x) {
+  if constexpr (D == 1) return dpp<0xB1>(x);                       // quad_perm 1,0,3,2
+  else if constexpr (D == 2) return dpp<0x4E>(x);                  // quad_perm 2,3,0,1
+  else if constexpr (D == 4) return dpp<0x1B>(dpp<0x141>(x));      // half mirror (^7), then ^3
+  else if constexpr (D == 8) return dpp<0x128>(x);                 // rotate a row of 16 by 8
+  else return __shfl_xor(x, D);
+}
+template <int G>
+__device__ __forceinline__ int lane_mirror(int x) {
+  if constexpr (G == 2) return dpp<0xB1>(x);
+  else if constexpr (G == 4) return dpp<0x1B>(x);
+  else if constexpr (G == 8) return dpp<0x141>(x);
+  else if constexpr (G == 16) return dpp<0x140>(x);
+  else return __shfl_xor(x, G - 1);
+}
+
+__device__ __forceinline__ double pack(int lo, int hi) {
+  return __hiloint2double(hi, lo);
+}
+template <int D>
+__device__ __forceinline__ double lane_xor(double x) {
+  return pack(lane_xor<D>(__double2loint(x)), lane_xor<D>(__double2hiint(x)));
+}
+template <int G>
+__device__ __forceinline__ double lane_mirror(double x) {
+  return pack(lane_mirror<G>(__double2loint(x)), lane_mirror<G>(__double2hiint(x)));
+}
+
+// The lane keeps the smaller (up false) or the larger of its value and p.
+__device__ __forceinline__ int keep(int x, int p, bool, int sel) { return med3_i32(x, p, sel); }
+__device__ __forceinline__ double keep(double x, double p, bool up, int) {
+  return (p < x) != up ? p : x;
+}
+__device__ __forceinline__ void order2(int& a, int& b) {
+  const int lo = a < b ? a : b, hi = a < b ? b : a;
+  a = lo;
+  b = hi;
+}
+__device__ __forceinline__ void order2(double& a, double& b) {
+  const double lo = fmin(a, b), hi = fmax(a, b);
+  a = lo;
+  b = hi;
+}
+
+// One exchange at lane distance D (after a merge's mirrored first exchange).
+template <int D, int R, class T>
+__device__ __forceinline__ void exchange_lanes(T (&x)[R], int lane) {
+  const bool up = (lane & D) != 0;
+  const int sel = up ? 0x7FFFFFFF : (int)0x80000000;
+#pragma unroll
+  for (int r = 0; r < R; ++r) x[r] = keep(x[r], lane_xor<D>(x[r]), up, sel);
+}
+// Exchanges at register distances R / 2 .. 1.
+template <int R, int FROM, class T>
+__device__ __forceinline__ void exchange_regs(T (&x)[R]) {
+#pragma unroll
+  for (int d = FROM; d >= 1; d >>= 1)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((r & d) == 0) order2(x[r], x[r | d]);
+}
+// Merge the two sorted halves of every group of G lanes (G R values).
+template <int G, int R, class T>
+__device__ __forceinline__ void merge_lanes(T (&x)[R], int lane) {
+  {
+    const bool up = (lane & (G >> 1)) != 0;
+    const int sel = up ? 0x7FFFFFFF : (int)0x80000000;
+#pragma unroll
+    for (int r = 0; r < R / 2; ++r) {
+      const T p = lane_mirror<G>(x[R - 1 - r]), q = lane_mirror<G>(x[r]);
+      x[r] = keep(x[r], p, up, sel);
+      x[R - 1 - r] = keep(x[R - 1 - r], q, up, sel);
+    }
+  }
+  if constexpr (G >= 64) exchange_lanes<16>(x, lane);
+  if constexpr (G >= 32) exchange_lanes<8>(x, lane);
+  if constexpr (G >= 16) exchange_lanes<4>(x, lane);
+  if constexpr (G >= 8) exchange_lanes<2>(x, lane);
+  if constexpr (G >= 4) exchange_lanes<1>(x, lane);
+  exchange_regs<R, R / 2>(x);
+}
+
+// Inclusive sum over the lanes of the wavefront.
+__device__ __forceinline__ int lane_scan(int v, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(v, d);
+    if (lane >= d) v += o;
+  }
+  return v;
+}
+
+// partial[3 block + 0..2] = S(A, B), S(A, A), S(B, B) of the block's C
+// dimensions.  Grid: ceil(dim / C) workgroups of C wavefronts.
+template <int R, int C>
+__global__ void __launch_bounds__(64 * C) sorted_pair_sum_kernel(
+    const float* __restrict__ A, int64_t lda, int n, const float* __restrict__ B, int64_t ldb,
+    int m, int64_t dim, int vec, double* __restrict__ partial) {
+  __shared__ float tile[64 * R * (C + 1)];           // [n + m][C + 1]
+  __shared__ double sums[3][C];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // neighbouring dimensions on one XCD (workgroups go to the 8 XCDs in turn),
+  // whose L2 then serves the 64-byte halves of a row's 128-byte lines
+  const int64_t nblk = gridDim.x;
+  const int64_t blk = (nblk % 8 == 0) ? (int64_t)(blockIdx.x % 8) * (nblk / 8) + blockIdx.x / 8
+                                      : (int64_t)blockIdx.x;
+  const int64_t k0 = blk * C;
+  constexpr int Q = C / 4;                           // 16-byte pieces of a row
+  const int q = (t % Q) * 4;
+  for (int row = t / Q; row < n + m; row += 64 * C / Q) {
+    const float* p = row < n ? A + (int64_t)row * lda + k0 + q : B + (int64_t)(row - n) * ldb + k0 + q;
+    float* d = tile + row * (C + 1) + q;
+    if (vec && k0 + q + 4 <= dim) {
+      const float4 v = *reinterpret_cast<const float4*>(p);
+      d[0] = v.x;
+      d[1] = v.y;
+      d[2] = v.z;
+      d[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] = k0 + q + e < dim ? p[e] : 0.0f;
+    }
+  }
+  __syncthreads();
+
+  const bool is_b = lane >= 32;
+  const int rows = is_b ? m : n, base = is_b ? n : 0;
+  int flags = 0;
+  int x[R];
+  bool finite = true;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = r * 32 + (lane & 31);
+    const float v = i < rows ? tile[(base + i) * (C + 1) + wave] : 3.402823466e38f;
+    finite = finite && fabsf(v) <= 3.402823466e38f;
+    x[r] = sort_key(v);
+  }
+  if (__any(!finite)) {                  // noted, and out of the other set's own sum
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float v = sort_value(x[r]);
+      if (!(fabsf(v) <= 3.402823466e38f)) {
+        flags |= v != v ? kSortFlagNan : v > 0.0f ? kSortFlagPos : kSortFlagNeg;
+        x[r] = 0;
+      }
+    }
+  }
+  // sort the R values of every lane, then lanes 0-31 (A) and 32-63 (B)
+#pragma unroll
+  for (int s = 2; s <= R; s <<= 1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((r & (s >> 1)) == 0) order2(x[r], x[r ^ (s - 1)]);
+#pragma unroll
+    for (int d = s >> 2; d >= 1; d >>= 1)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if ((r & d) == 0) order2(x[r], x[r | d]);
+  }
+  merge_lanes<2>(x, lane);
+  merge_lanes<4>(x, lane);
+  merge_lanes<8>(x, lane);
+  merge_lanes<16>(x, lane);
+  merge_lanes<32>(x, lane);
+  // merge A with B, each value marked in its lowest bit
+  double z[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const double v = (double)sort_value(x[r]);
+    z[r] = pack(__double2loint(v) | (is_b ? 1 : 0), __double2hiint(v));
+  }
+  merge_lanes<64>(z, lane);
+
+  int nb = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) nb += __double2loint(z[r]) & 1;
+  int b = lane_scan(nb, lane) - nb;                  // values of B before this lane's
+  const double first = pack(__double2loint(z[0]) & ~1, __double2hiint(z[0]));
+  const double after = pack(__shfl_down(__double2loint(first), 1), __shfl_down(__double2hiint(first), 1));
+  double sxy = 0.0, sxx = 0.0, syy = 0.0;
+  double v = first;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int k = lane * R + r;                      // position in the merged order
+    b += __double2loint(z[r]) & 1;
+    const int a = k + 1 - b;
+    const double w = r + 1 < R ? pack(__double2loint(z[r + 1 < R ? r + 1 : r]) & ~1,
+                                      __double2hiint(z[r + 1 < R ? r + 1 : r]))
+                               : after;
+    const double gap = k + 1 < n + m ? w - v : 0.0;  // the padding has no gaps
+    const int an = __mul24(a, n - a), bm = __mul24(b, m - b);
+    const int ab = __mul24(a, m - b) + __mul24(b, n - a);
+    sxy = fma(gap, (double)ab, sxy);
+    sxx = fma(gap, (double)(2 * an), sxx);
+    syy = fma(gap, (double)(2 * bm), syy);
+    v = w;
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    sxy += __shfl_xor(sxy, d);
+    sxx += __shfl_xor(sxx, d);
+    syy += __shfl_xor(syy, d);
+  }
+  // what |x - y| gives where values are not finite: a set's own sum has the
+  // pair of a value with itself (inf - inf), two sets' sum has infinities of
+  // equal sign
+  const unsigned long long lo = 0xFFFFFFFFull;
+  const unsigned long long fn = __ballot(flags & kSortFlagNan), fp = __ballot(flags & kSortFlagPos),
+                           fm = __ballot(flags & kSortFlagNeg);
+  if (fn | fp | fm) {
+    const double nan = __longlong_as_double(0x7FF8000000000000ll);
+    if ((fn | fp | fm) & lo) sxx = nan;
+    if ((fn | fp | fm) >> 32) syy = nan;
+    const bool same = ((fp & lo) && (fp >> 32)) || ((fm & lo) && (fm >> 32));
+    sxy = fn || same ? nan : __longlong_as_double(0x7FF0000000000000ll);
+  }
+  if (lane == 0) {
+    sums[0][wave] = sxy;
+    sums[1][wave] = sxx;
+    sums[2][wave] = syy;
+  }
+  __syncthreads();
+  if (t < 3) {
+    double s = 0.0;
+    for (int c = 0; c < C; ++c)
+      if (k0 + c < dim) s += sums[t][c];
+    partial[3 * blk + t] = s;
+  }
+}
+
+// The blocks' sums in order: with mmd, out[0..3] = {MMD, S(A, B), S(A, A),
+// S(B, B)}; without, out[0] = S(A, B).
+__global__ void __launch_bounds__(256) sorted_final_kernel(const double* __restrict__ partial,
+                                                           int64_t count, int64_t n, int64_t m,
+                                                           int mmd, double* __restrict__ out) {
+  __shared__ double red[3][256];
+  const int t = threadIdx.x;
+  double s[3] = {0.0, 0.0, 0.0};
+  for (int64_t i = t; i < count; i += 256)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s[k] += partial[3 * i + k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) red[k][t] = s[k];
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) red[k][t] += red[k][t + w];
+    __syncthreads();
+  }
+  if (t == 0) {
+    if (mmd) {
+      const double dn = (double)n, dm = (double)m;
+      out[0] = 2.0 * red[0][0] / (dn * dm) - red[1][0] / (dn * dn) - red[2][0] / (dm * dm);
+      out[1] = red[0][0];
+      out[2] = red[1][0];
+      out[3] = red[2][0];
+    } else {
+      out[0] = red[0][0];
+    }
+  }
+}
+
+// Registers per lane for sets of at most 32 R values; 0 beyond 2048.
+int sort_regs(int64_t n, int64_t m) {
+  const int64_t top = n > m ? n : m;
+  int r = 4;
+  while (r < 64 && 32 * r < top) r *= 2;
+  return 32 * r >= top ? r : 0;
+}
+// Dimensions per workgroup: 16 (64 bytes of a row); 8 at R = 64, whose 4096
+// rows fill the LDS, and at R = 32, where two workgroups of 70 KB share a CU
+// and one stages while the other sorts (1000 x 1000: 85 -> 79 us).
+int sort_cols(int r) { return r >= 32 ? 8 : 16; }
+
+// The three sums of an MMD are sorted whenever the registers hold the sets:
+// one pass against three launches over all pairs (8192 features, us: 64 x 64
+// sounds 88 -> 15, 1 x 1 of one feature 25 -> 12, 2000 x 2000 5320 -> 204,
+// and, the closest, 2000 x 2000 of 8 features 45 against 48).
+bool sort_mmd(int64_t n, int64_t m, int64_t dim) {
+  return n > 0 && m > 0 && dim > 0 && sort_regs(n, m) > 0;
+}
+
+int64_t tiled(int64_t n) { return (n + kPT - 1) / kPT * kPT; }
+
+// One sum alone is sorted up to 256 sounds, where both ways are bound by their
+// two launches or the sort is ahead (64 x 64: 29 -> 15 us, 256 x 64: 29 ->
+// 22), and beyond where its pairs (in whole tiles) outweigh sorting the longer
+// set: at 1000 x 64 all pairs take 31 us and the sort 74, at 1000 x 256 116
+// and 75, at 2000 x 64 64 and 191, at 2000 x 256 226 and 192.
+bool sort_one(int64_t n, int64_t m, int64_t dim) {
+  const int r = sort_regs(n, m);
+  return sort_mmd(n, m, dim) && (r <= 8 || tiled(n) * tiled(m) >= 6400 * (int64_t)r);
+}
+
+template <int R, int C>
+hipError_t launch_sorted(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
+                         int64_t m, int64_t dim, int vec, double* partial, int64_t blocks,
+                         hipStream_t s) {
+  hipLaunchKernelGGL((sorted_pair_sum_kernel<R, C>), dim3((unsigned)blocks), dim3(64 * C), 0, s, A,
+                     lda, (int)n, B, ldb, (int)m, dim, vec, partial);
+  return hipGetLastError();
+}
+
+hipError_t launch_sort_sums(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
+                            int64_t m, int64_t dim, double* partial, int mmd, double* out,
+                            hipStream_t s) {
+  const int r = sort_regs(n, m);
+  const int64_t blocks = (dim + sort_cols(r) - 1) / sort_cols(r);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const int vec = ((lda | ldb) % 4 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0) &&
+                  (reinterpret_cast<uintptr_t>(B) % 16 == 0);
+  hipError_t e;
+  switch (r) {
+    case 4: e = launch_sorted<4, 16>(A, lda, n, B, ldb, m, dim, vec, partial, blocks, s); break;
+    case 8: e = launch_sorted<8, 16>(A, lda, n, B, ldb, m, dim, vec, partial, blocks, s); break;
+    case 16: e = launch_sorted<16, 16>(A, lda, n, B, ldb, m, dim, vec, partial, blocks, s); break;
+    case 32: e = launch_sorted<32, 8>(A, lda, n, B, ldb, m, dim, vec, partial, blocks, s); break;
+    default: e = launch_sorted<64, 8>(A, lda, n, B, ldb, m, dim, vec, partial, blocks, s); break;
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sorted_final_kernel, dim3(1), dim3(256), 0, s, partial, blocks, n, m, mmd, out);
+  return hipGetLastError();
+}
+
+size_t sort_bytes(int64_t n, int64_t m, int64_t dim) {
+  const int c = sort_cols(sort_regs(n, m));
+  return (size_t)((dim + c - 1) / c) * 3 * sizeof(double);
+}
+
+hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
+                            int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
   const PairPlan p = pair_plan(n, m, dim);
   const int64_t blocks = p.tiles_n * p.tiles_m * p.shares;
   if (blocks > 0 && dim > 0) {
@@ -192,7 +574,41 @@ hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const floa
   return hipGetLastError();
 }
 
-hipError_t launch_mmd_combine(double* out, int64_t n, int64_t m, hipStream_t s) {
+}  // namespace
+
+size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
+  if (sort_one(n, m, dim)) return sort_bytes(n, m, dim);
+  const PairPlan p = pair_plan(n, m, dim);
+  return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+}
+
+hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
+                              int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
+  if (sort_one(n, m, dim))
+    return launch_sort_sums(A, lda, n, B, ldb, m, dim, partial, 0, out, s);
+  return launch_all_pairs(A, lda, n, B, ldb, m, dim, partial, out, s);
+}
+
+size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
+  if (sort_mmd(n, m, dim))
+    return sort_bytes(n, m, dim);
+  size_t need = 0;
+  for (const PairPlan& p : {pair_plan(n, m, dim), pair_plan(n, n, dim), pair_plan(m, m, dim)}) {
+    const size_t b = (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+    need = b > need ? b : need;
+  }
+  return need;
+}
+
+hipError_t launch_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,
+                         double* ws, double* out, hipStream_t s) {
+  if (sort_mmd(n, m, dim))
+    return launch_sort_sums(X, dim, n, Y, dim, m, dim, ws, 1, out, s);
+  // the three sums reuse the workspace in stream order
+  hipError_t e = launch_all_pairs(X, dim, n, Y, dim, m, dim, ws, out + 1, s);
+  if (e == hipSuccess) e = launch_all_pairs(X, dim, n, X, dim, n, dim, ws, out + 2, s);
+  if (e == hipSuccess) e = launch_all_pairs(Y, dim, m, Y, dim, m, dim, ws, out + 3, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(mmd_combine_kernel, dim3(1), dim3(64), 0, s, out, n, m);
   return hipGetLastError();
 }

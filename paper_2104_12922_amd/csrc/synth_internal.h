@@ -105,7 +105,9 @@ hipError_t launch_scale_rows(const float* g, const double* sc, int64_t rows, int
 size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim);
 hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                               int64_t m, int64_t dim, double* partial, double* out, hipStream_t s);
-hipError_t launch_mmd_combine(double* out, int64_t n, int64_t m, hipStream_t s);
+size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim);
+hipError_t launch_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,
+                         double* ws, double* out, hipStream_t s);
 hipError_t launch_fm_render(const float* params, const int64_t* offsets, int64_t batch,
                             int64_t n_samples, float* audio, double sr, double rc, int q,
                             const NebulaArgs& neb, const int32_t* order, hipStream_t s);
