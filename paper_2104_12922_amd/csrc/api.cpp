@@ -260,7 +260,7 @@ int render_plan_impl(const synth_config* cfg, const float* params, const uint64_
                      uint64_t first_g, int64_t batch, const int64_t* offsets, int64_t n_samples,
                      int64_t max_samples, float* audio, int runs_per_segment,
                      int slices_per_voice, int persistent, int grid_blocks, const int32_t* order,
-                     void* workspace, size_t workspace_bytes, void* stream) {
+                     void* workspace, size_t workspace_bytes, void* stream, int pass_split = 1) {
   if (batch < 0) return SYNTH_EINVAL;
   RenderArgs a;
   bool clamp = false;
@@ -279,7 +279,7 @@ int render_plan_impl(const synth_config* cfg, const float* params, const uint64_
     const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
     if (slices_per_voice > nchunks) return SYNTH_EUNSUPPORTED;
   }
-  const int64_t items = batch * (int64_t)slices_per_voice;
+  const int64_t items = batch * (int64_t)slices_per_voice * pass_split;
   if (items > 0x7FFFFFFF) return SYNTH_EINVAL;
 
   a.params = params;
@@ -290,6 +290,7 @@ int render_plan_impl(const synth_config* cfg, const float* params, const uint64_
   a.n_uniform = offsets ? 0 : n_samples;
   a.batch = batch;
   a.slices = slices_per_voice;
+  a.pass_split = pass_split;
   a.order = order;
   if (order && batch > 0x7FFFFFFF) return SYNTH_EINVAL;
   int grid = (int)items;
@@ -353,20 +354,31 @@ namespace {
 // of 4); small uniform batches split each voice over workgroups so that the
 // grid covers the chip - at most a quarter of its chunks when the slices
 // walk the earlier chunks for their carries, up to all of them when the
-// carries are computed first.
+// carries are computed first, and then as many again, per chunk, as there are
+// passes (4) while the chip has fewer than two workgroups per CU (each forms
+// the chunk's control stage for itself, so only where no carries are walked).
+// With carries the aim is 8192 workgroups as soon as a voice is split (256
+// voices of 4 s: 139 us with 2048, 129 with 8192; 512: 303 and 270); the
+// passes halve the render of 8 voices of 1 s (25 -> 16 us).
 void default_plan(const synth_config* cfg, int64_t batch, const int64_t* offsets,
-                  int64_t n_samples, bool carried, int* rps, int* slices) {
+                  int64_t n_samples, bool carried, int* rps, int* slices,
+                  int* pass_split = nullptr) {
   *slices = 1;
   *rps = 4;
+  if (pass_split) *pass_split = 1;
   if (!cfg || !(cfg->control_rate > 0.0)) return;
   const double q = nearbyint(cfg->sample_rate / cfg->control_rate);
   if (fmod(q, 4.0) != 0.0) *rps = 1;
   if (!offsets && n_samples > 0 && batch > 0 && q >= 4.0) {
     const int64_t nchunks = chunks_of(n_samples, (int)q);
     int64_t want = (2048 + batch - 1) / batch;
+    if (carried && want > 1) want = (8192 + batch - 1) / batch;
     const int64_t cap = carried ? nchunks : nchunks / 4;
     if (want > cap) want = cap;
     if (want > 1) *slices = (int)want;
+    if (pass_split && *rps == 4 && (carried ? want > 1 : nchunks == 1)) {
+      while (*pass_split < 4 && batch * want * *pass_split < 512) *pass_split *= 2;
+    }
   }
 }
 }  // namespace
@@ -374,10 +386,10 @@ void default_plan(const synth_config* cfg, int64_t batch, const int64_t* offsets
 int synth_render(const synth_config* cfg, const float* params, const uint64_t* voice_ids,
                  uint64_t first_g, int64_t batch, const int64_t* offsets, int64_t n_samples,
                  float* audio, void* stream) {
-  int rps, slices;
-  default_plan(cfg, batch, offsets, n_samples, false, &rps, &slices);
-  return synth_render_plan(cfg, params, voice_ids, first_g, batch, offsets, n_samples, audio, rps,
-                           slices, 0, 0, stream);
+  int rps, slices, pass_split;
+  default_plan(cfg, batch, offsets, n_samples, false, &rps, &slices, &pass_split);
+  return render_plan_impl(cfg, params, voice_ids, first_g, batch, offsets, n_samples, 0, audio, rps,
+                          slices, 0, 0, nullptr, nullptr, 0, stream, pass_split);
 }
 
 size_t synth_render_workspace(const synth_config* cfg, int64_t batch, int64_t n_samples) {
@@ -393,10 +405,11 @@ int synth_render_ws(const synth_config* cfg, const float* params, const uint64_t
   if (!workspace || offsets) {
     return synth_render(cfg, params, voice_ids, first_g, batch, offsets, n_samples, audio, stream);
   }
-  int rps, slices;
-  default_plan(cfg, batch, offsets, n_samples, true, &rps, &slices);
+  int rps, slices, pass_split;
+  default_plan(cfg, batch, offsets, n_samples, true, &rps, &slices, &pass_split);
   return render_plan_impl(cfg, params, voice_ids, first_g, batch, offsets, n_samples, n_samples,
-                          audio, rps, slices, 0, 0, nullptr, workspace, workspace_bytes, stream);
+                          audio, rps, slices, 0, 0, nullptr, workspace, workspace_bytes, stream,
+                          pass_split);
 }
 
 // ---------------------------------------------------------------------------

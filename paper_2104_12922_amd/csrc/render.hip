@@ -95,8 +95,10 @@ __device__ __forceinline__ void noise_group(float* out, const float* tile, int g
   }
 }
 
+// Slice `slice` of voice b; of its passes those p with p mod a.pass_split ==
+// sub, and that share of its silent samples.
 template <int RPS, bool CLAMP>
-__device__ void render_item(const RenderArgs& a, int64_t b, int slice, VoiceShared& sh,
+__device__ void render_item(const RenderArgs& a, int64_t b, int slice, int sub, VoiceShared& sh,
                             float* tile) {
   const int lane = threadIdx.x;
   const int q = a.q;
@@ -161,7 +163,13 @@ __device__ void render_item(const RenderArgs& a, int64_t b, int slice, VoiceShar
     if (c >= c_sil) {
       const int64_t z0 = (c > c_lo ? c : c_lo) * (int64_t)kSegsPerChunk * q;
       const int64_t z1 = c_hi * (int64_t)kSegsPerChunk * q < N ? c_hi * (int64_t)kSegsPerChunk * q : N;
-      zero_fill(out, z0, z1, lane, aligned);
+      if (a.pass_split > 1) {
+        const int64_t per = ((z1 - z0) / a.pass_split + 3) & ~(int64_t)3;
+        const int64_t s0 = z0 + sub * per;
+        zero_fill(out, s0, sub + 1 < a.pass_split && s0 + per < z1 ? s0 + per : z1, lane, aligned);
+      } else {
+        zero_fill(out, z0, z1, lane, aligned);
+      }
       break;
     }
     // ---------------- control stage: lane = control sample j ----------------
@@ -184,7 +192,7 @@ __device__ void render_item(const RenderArgs& a, int64_t b, int slice, VoiceShar
     const int nseg = (int)((J - c * kSegsPerChunk) < kSegsPerChunk ? (J - c * kSegsPerChunk)
                                                                     : kSegsPerChunk);
     const int npass = (nseg + segs_pp - 1) / segs_pp;
-    for (int p = 0; p < npass; ++p) {
+    for (int p = sub; p < npass; p += a.pass_split) {
       const int ls = p * segs_pp + lane / RPS;   // chunk-local segment of this lane's run
       const int m = lane % RPS;                  // run within the segment
       const int src = ls < kWave ? ls : kWave - 1;
@@ -265,75 +273,84 @@ template <int RPS, bool CLAMP>
 __global__ void __launch_bounds__(kWave) render_kernel(const RenderArgs a) {
   __shared__ VoiceShared sh;
   extern __shared__ __align__(16) float tile[];
-  const int64_t nitems = a.batch * a.slices;
-  for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x)
-  {
-    const int64_t k = item / a.slices;
+  const int per = a.slices * a.pass_split;     // workgroups per voice
+  const int64_t nitems = a.batch * per;
+  for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
+    const int64_t k = item / per;
+    const int part = (int)(item % per);
     const int64_t b = a.order ? (int64_t)a.order[k] : k;
-    if (b >= 0 && b < a.batch) render_item<RPS, CLAMP>(a, b, (int)(item % a.slices), sh, tile);
+    if (b >= 0 && b < a.batch)
+      render_item<RPS, CLAMP>(a, b, part / a.pass_split, part % a.pass_split, sh, tile);
   }
 }
 
 // Chunk-start carries for launches that split voices over workgroups: the
 // LFO and VCO phases the control stage carries from chunk to chunk, at the
-// start of every chunk, without walking the chunks one after another.  Each
-// chunk's raw sums come from its own control stage (one wavefront per chunk
-// and voice); one wavefront per voice then applies the updates
-// carry' = (carry + t) - floor(carry + t) in chunk order, the same float64
-// operations the walk performs, so a split render is bit-identical to an
-// unsplit one.  Pass 0 takes the LFO sums (the LFO rates depend on envelopes
-// only: just those envelopes are evaluated), pass 1 the VCO sums given the
-// LFO carries.
-template <int RPS, bool CLAMP, int PASS>
-__global__ void __launch_bounds__(kWave) carry_sums_kernel(const RenderArgs a, double* carries,
-                                                           int64_t stride) {
-  __shared__ VoiceShared sh;
-  __shared__ double envs[8 * kWave];
-  const int lane = threadIdx.x;
-  const int64_t c = blockIdx.x, b = blockIdx.y;
-  int64_t off0 = 0, N = a.n_uniform;
-  if (a.offsets) packed_range(a.offsets, a.batch, b, off0, N);
-  const int64_t J = (N + a.q - 1) / a.q;
-  const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
-  if (N <= 0 || c >= nchunks) return;
-  voice_setup(a, b, sh, lane);
-  double* cr = carries + (b * stride + c) * 4;
-  if (PASS == 1 && lane < 2) sh.carry[lane] = cr[lane];
-  __syncthreads();
-  double y[5], yn[5], tl[4];
-  if (PASS == 0)
-    lfo_chunk_sums(a, sh, c, lane, tl);
-  else
-    control_stage<RPS, CLAMP>(a, sh, envs, c, J, a.q / RPS, lane, y, yn, tl);
-  if (lane == 0) {
-    cr[2 * PASS] = tl[2 * PASS];
-    cr[2 * PASS + 1] = tl[2 * PASS + 1];
-  }
-}
+// start of every chunk, without walking the chunks one after another.  One
+// workgroup per voice, a wavefront per chunk, up to 16 chunks at a time: each
+// forms its chunk's raw LFO sums (the LFO rates depend on envelopes only),
+// then, from everyone's sums, the LFO phases at its start and its raw VCO sums,
+// then the VCO phases.  The updates carry' = (carry + t) - floor(carry + t) are
+// applied in chunk order by every wavefront for itself, the float64 operations
+// the walk performs, so a split render is bit-identical to an unsplit one.
+// Bound by the latency of the float64 chains; as two sum passes and two scans
+// in four launches, with the voice's parameters mapped in every workgroup and
+// the control stage's outputs formed for nothing, 256 voices of 4 s took 75 us
+// and 8 of 1 s 32.
+constexpr int kCarryWaves = 16;
 
-template <int PASS>
-__global__ void __launch_bounds__(kWave) carry_scan_kernel(const RenderArgs a, double* carries,
-                                                           int64_t stride) {
+template <int RPS, bool CLAMP>
+__global__ void __launch_bounds__(kWave* kCarryWaves) voice_carries_kernel(const RenderArgs a,
+                                                                          double* carries,
+                                                                          int64_t stride) {
   __shared__ VoiceShared sh;
-  const int lane = threadIdx.x;
+  __shared__ double scratch[kCarryWaves][8 * kWave];
+  __shared__ double tl[4][kCarryWaves];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int waves = blockDim.x / kWave;
   const int64_t b = blockIdx.x;
   int64_t off0 = 0, N = a.n_uniform;
   if (a.offsets) packed_range(a.offsets, a.batch, b, off0, N);
-  const int64_t J = (N + a.q - 1) / a.q;
-  const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
   if (N <= 0) return;
-  voice_setup(a, b, sh, lane);
-  if (lane < 2) {
-    const int k = 2 * PASS + lane;
-    double cy = sh.carry[k];
-    const int64_t nc_max = nchunks < stride ? nchunks : stride;
-    for (int64_t c = 0; c < nc_max; ++c) {
-      double* cr = carries + (b * stride + c) * 4;
-      const double t = cr[k];
-      cr[k] = cy;
-      const double nc = cy + t;
-      cy = nc - floor(nc);
+  const int64_t J = (N + a.q - 1) / a.q;
+  int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
+  if (nchunks > stride) nchunks = stride;
+  voice_setup(a, b, sh, threadIdx.x);
+  double block[4];                       // the phases at chunk `base`
+#pragma unroll
+  for (int k = 0; k < 4; ++k) block[k] = sh.carry[k];
+  for (int64_t base = 0; base < nchunks; base += waves) {
+    const int64_t c = base + wave;
+    const int n = (int)(nchunks - base < waves ? nchunks - base : waves);
+    double mine[4];                      // the phases at chunk c
+#pragma unroll
+    for (int step = 0; step < 2; ++step) {
+      if (c < nchunks) {
+        double t[2];
+        if (step == 0)
+          lfo_chunk_sums(a, sh.v, sh.d, scratch[wave], c, lane, t);
+        else
+          vco_chunk_sums<RPS, CLAMP>(a, sh.v, sh.d, scratch[wave], c, J, a.q / RPS, lane, mine, t);
+        if (lane == 0) {
+          tl[2 * step][wave] = t[0];
+          tl[2 * step + 1][wave] = t[1];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int k = 2 * step; k < 2 * step + 2; ++k) {
+        mine[k] = block[k];
+        for (int i = 0; i < n; ++i) {
+          if (i == wave) mine[k] = block[k];
+          const double nc = block[k] + tl[k][i];
+          block[k] = nc - floor(nc);
+        }
+      }
     }
+    if (c < nchunks && lane < 4)
+      carries[(b * stride + c) * 4 + lane] =
+          lane == 0 ? mine[0] : lane == 1 ? mine[1] : lane == 2 ? mine[2] : mine[3];
+    __syncthreads();                     // tl is read before the next chunks' sums
   }
 }
 
@@ -391,13 +408,9 @@ hipError_t launch_render(const RenderArgs& a, int runs_per_segment, bool clamp, 
 
 template <int RPS, bool CLAMP>
 hipError_t carries_rps(const RenderArgs& a, double* carries, int64_t stride, hipStream_t s) {
-  const dim3 grid((unsigned)stride, (unsigned)a.batch);
-  hipLaunchKernelGGL((carry_sums_kernel<RPS, CLAMP, 0>), grid, dim3(kWave), 0, s, a, carries, stride);
-  hipLaunchKernelGGL((carry_scan_kernel<0>), dim3((unsigned)a.batch), dim3(kWave), 0, s, a, carries,
-                     stride);
-  hipLaunchKernelGGL((carry_sums_kernel<RPS, CLAMP, 1>), grid, dim3(kWave), 0, s, a, carries, stride);
-  hipLaunchKernelGGL((carry_scan_kernel<1>), dim3((unsigned)a.batch), dim3(kWave), 0, s, a, carries,
-                     stride);
+  const int waves = stride < kCarryWaves ? (int)stride : kCarryWaves;
+  hipLaunchKernelGGL((voice_carries_kernel<RPS, CLAMP>), dim3((unsigned)a.batch), dim3(kWave * waves),
+                     0, s, a, carries, stride);
   return hipGetLastError();
 }
 

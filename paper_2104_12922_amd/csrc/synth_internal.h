@@ -47,7 +47,8 @@ struct RenderArgs {
   double nyq_midi;           // pitch (MIDI) above which f > sr / 2
   int q;                     // audio samples per control sample
   uint32_t q_magic;          // ceil(2^32 / q): x / q == umulhi(x, q_magic) for x < 2^16
-  int slices;                // workgroups per voice (uniform lengths only)
+  int slices;                // parts of a voice's chunks rendered by workgroups of their own
+  int pass_split;            // >= 1: workgroups that share a slice's passes
   int persistent_grid;       // >0: workgroup w renders voices w, w+grid, ...
   int mix_mode;
   uint32_t nk0, nk1;         // noise key

@@ -303,12 +303,17 @@ __device__ __forceinline__ double adsr_value(const double* dv, int k, double jd,
   return pow01(att, al) * (S + (1.0 - S) * pow01(1.0 - dec, al)) * pow01(1.0 - rel, al);
 }
 
-// The raw LFO chunk sums of control_stage (tl[0], tl[1]) alone: the rate
-// ADSRs and the rate scan, with the same float64 operations.
-__device__ inline void lfo_chunk_sums(const RenderArgs& a, const VoiceShared& sh, int64_t c,
-                                      int lane, double* tl) {
-  const double* v = sh.v;
-  const double* dv = sh.d;
+// The raw sums control_stage's phase carries advance by (LFO 1, LFO 2, VCO 1,
+// VCO 2: the exclusive scans at lane 62), with its float64 operations and
+// nothing else of it.  Only wavefront operations, so the wavefronts of a
+// workgroup may take different chunks.  In two steps, because the VCO sums
+// need the LFO phases at the chunk's start: the first leaves the rate
+// envelopes and the rate scans of the chunk in the wavefront's scratch ws
+// (8 x 64 doubles).
+enum { kCsEnv = 0, kCsLfo = 2, kCsScan = 4, kCsAmp = 6 };
+
+__device__ inline void lfo_chunk_sums(const RenderArgs& a, const double* v, const double* dv,
+                                      double* ws, int64_t c, int lane, double tl[2]) {
   const double rc = a.rc;
   const double note_off = v[1] * rc;
   const double jd = (double)(c * kSegsPerChunk + lane);
@@ -318,8 +323,80 @@ __device__ inline void lfo_chunk_sums(const RenderArgs& a, const VoiceShared& sh
     const double f = fmax(0.0, v[pb] + v[pb + 1] * adsr_value(dv, 2 + 2 * i, jd, note_off));
     const double inc = lane < kPointsPerChunk - 1 ? f / rc : 0.0;
     const double sc = wave_excl_scan(inc, lane);
-    const double s62 = __shfl(sc, kSegsPerChunk);
-    if (lane == 0) tl[i] = s62;
+    ws[(kCsScan + i) * kWave + lane] = sc;
+    if (i == 0) tl[0] = __shfl(sc, kSegsPerChunk);
+    else tl[1] = __shfl(sc, kSegsPerChunk);
+  }
+}
+
+// The VCO sums given the LFO phases carry[0..1] at the chunk's start.
+template <int RPS, bool CLAMP>
+__device__ inline void vco_chunk_sums(const RenderArgs& a, const double* v, const double* dv,
+                                      double* ws, int64_t c, int64_t J, int h, int lane,
+                                      const double carry[2], double tl[2]) {
+  const double rc = a.rc, sr = a.sr;
+  const int q = a.q;
+  const double qd = (double)q, hd = (double)h;
+  const double note_off = v[1] * rc;
+  const double midi = v[0];
+  const int64_t j = c * kSegsPerChunk + lane;
+  const double jd = (double)j;
+#pragma unroll 1
+  for (int k = 0; k < 4; ++k) {         // adsr_1, adsr_2 and the LFOs' amplitude ADSRs
+    const double e = adsr_value(dv, k < 2 ? k : 2 * k - 1, jd, note_off);
+    ws[(k < 2 ? kCsEnv + k : kCsAmp + k - 2) * kWave + lane] = e;
+  }
+#pragma unroll 1
+  for (int i = 0; i < 2; ++i) {
+    const int pb = 32 + 8 * i;
+    const double th = (i == 0 ? carry[0] : carry[1]) + ws[(kCsScan + i) * kWave + lane];
+    const double ph = th - floor(th);
+    const double num = v[pb + 3] * ((1.0 + sin_cycles_f64(ph)) / 2.0) +
+                       v[pb + 4] * (1.0 - fabs(2.0 * ph - 1.0)) + v[pb + 5] * ph +
+                       v[pb + 6] * (1.0 - ph) + v[pb + 7] * (ph < 0.5 ? 1.0 : 0.0);
+    ws[(kCsLfo + i) * kWave + lane] = (num * dv[kLfoInvW + i]) * ws[(kCsAmp + i) * kWave + lane];
+  }
+  const double x0 = ws[lane], x1 = ws[kWave + lane];
+  const double x2 = ws[2 * kWave + lane], x3 = ws[3 * kWave + lane];
+  const bool last = (j + 1 >= J);
+#pragma unroll 1
+  for (int vc = 0; vc < 2; ++vc) {
+    const int tb = vc ? 71 : 68;
+    const int o = 2 * vc, pb = 48 + 4 * o;
+    const double acc = v[pb] * x0 + v[pb + 1] * x1 + v[pb + 2] * x2 + v[pb + 3] * x3;
+    const double ya = acc * dv[kMixInvNorm + o];
+    const double yd = __shfl_down(ya, 1);
+    const double yb = last ? ya : yd;
+    const double base = midi + v[tb];
+    const double m0 = base + v[tb + 1] * ya;
+    const double m1 = base + v[tb + 1] * yb;
+    const double i0 = 440.0 * exp2_f64((m0 - 69.0) * (1.0 / 12.0)) / sr;
+    const double Lr = (m1 - m0) * (kLn2 / (12.0 * qd));
+    const double e1 = expm1_f64(Lr);
+    const double eh = expm1_f64(Lr * hd);
+    const double Rh = 1.0 + eh;
+    const double Sh = (e1 == 0.0) ? i0 * hd : i0 * (eh / e1);
+    double S;
+    if constexpr (CLAMP) {
+      const double rr = 1.0 + e1;
+      S = 0.0;
+      double inc = i0;
+      for (int k = 0; k < q; ++k) {
+        S += fmin(inc, 0.5);
+        inc *= rr;
+      }
+    } else {
+      S = Sh;
+      double t = Sh;
+#pragma unroll
+      for (int m = 1; m < RPS; ++m) {
+        t *= Rh;
+        S += t;
+      }
+    }
+    const double sc = wave_excl_scan(lane < kSegsPerChunk ? S : 0.0, lane);
+    if (vc == 0) tl[0] = __shfl(sc, kSegsPerChunk);
+    else tl[1] = __shfl(sc, kSegsPerChunk);
   }
 }
 
@@ -330,12 +407,8 @@ __device__ inline void lfo_chunk_sums(const RenderArgs& a, const VoiceShared& sh
 // (lane < 62) the oscillator data sh.seg; advances the LFO and VCO phase
 // carries to the next chunk.  All 64 lanes call it.
 template <int RPS, bool CLAMP>
-//   tl (optional): receives the four raw chunk sums the carries advance by
-//   (LFO 1, LFO 2, VCO 1, VCO 2: the exclusive scans at lane 62), so that
-//   carry' = (carry + tl) - floor(carry + tl) reproduces this chunk's update.
 __device__ inline void control_stage(const RenderArgs& a, VoiceShared& sh, double* envs, int64_t c,
-                                     int64_t J, int h, int lane, double y[5], double yn[5],
-                                     double* tl = nullptr) {
+                                     int64_t J, int h, int lane, double y[5], double yn[5]) {
   const double* v = sh.v;
   const double* dv = sh.d;
   const double rc = a.rc, sr = a.sr;
@@ -358,10 +431,6 @@ __device__ inline void control_stage(const RenderArgs& a, VoiceShared& sh, doubl
     const double inc = lane < kPointsPerChunk - 1 ? f / rc : 0.0;
     const double sc = wave_excl_scan(inc, lane);
     const double th = sh.carry[i] + sc;
-    if (tl) {
-      const double s62 = __shfl(sc, kSegsPerChunk);
-      if (lane == 0) tl[i] = s62;
-    }
     const double ph = th - floor(th);
     const double num = v[pb + 3] * ((1.0 + sin_cycles_f64(ph)) / 2.0) +
                        v[pb + 4] * (1.0 - fabs(2.0 * ph - 1.0)) + v[pb + 5] * ph +
@@ -422,10 +491,6 @@ __device__ inline void control_stage(const RenderArgs& a, VoiceShared& sh, doubl
     }
     const double sc = wave_excl_scan(lane < kSegsPerChunk ? S : 0.0, lane);
     const double th = sh.carry[2 + vc] + sc;
-    if (tl) {
-      const double s62 = __shfl(sc, kSegsPerChunk);
-      if (lane == 0) tl[2 + vc] = s62;
-    }
     sh.seg[vc][kSegTheta][lane] = th - floor(th);
     sh.seg[vc][kSegInc][lane] = i0;
     sh.seg[vc][kSegRatio][lane] = rr;
