@@ -21,7 +21,12 @@
 // segment of 19 hops.  Kernel 2 adds, for every sample, the (at most two)
 // segments that cover it per resolution in a fixed order, and sums the
 // per-workgroup loss partials in a fixed order: bitwise deterministic, no
-// atomics.
+// atomics.  Bound by VALU issue (the FFTs) and their LDS exchanges; loss and
+// gradient of 256 voices of 4 s against cached targets 1487 -> 1269 us with
+// the inverse's input formed from registers (H went through LDS, two reads a
+// point), the overlap-add two samples at a time with uniform frame tests, and
+// the halvings folded into the window.  A workgroup that keeps its tables and
+// takes several chunks in turn was 5% slower here (1378 -> 1446 at that point).
 #include <math.h>
 
 #include "synth_internal.h"
@@ -60,24 +65,25 @@ template <int Nc>
 struct MrShared {
   static constexpr int ola_slots = 4 * Nc;   // >= the 7 hops of four frames
   float2 buf[kMrWaves][Nc];    // one FFT buffer per wavefront
-  alignas(8) float win[2 * Nc];  // periodic Hann window
+  alignas(8) float win[2 * Nc];  // half the periodic Hann window: the 1/2 of the real split
+                                 // (exact) and of the gradient rows
   float2 rs[Nc / 2 + 1];       // exp(-2 pi i k / n), k <= n / 4 (real split)
   float2 pt[wfft::pt_size<Nc>()];   // FFT pass twiddles
-  float ola[ola_slots];        // overlap-add accumulator
+  alignas(8) float ola[ola_slots];   // overlap-add accumulator
   double red[kMrWaves];
 };
 
 // Bins k and Nc - k (k < Nc / 2) of the real spectrum of a frame whose
 // half-size complex FFT Z is in buf: X_k = E + W O, X_{Nc-k} = conj(E - W O)
-// with E = (Z_k + conj Z_{Nc-k}) / 2, O = -i (Z_k - conj Z_{Nc-k}) / 2,
-// W = exp(-2 pi i k / n).  k = Nc / 2 gives X_{Nc/2} in the first output.
+// with E = Z_k + conj Z_{Nc-k}, O = -i (Z_k - conj Z_{Nc-k}) (their 1/2 is in
+// the window), W = exp(-2 pi i k / n).  k = Nc / 2 gives X_{Nc/2} in the first output.
 template <int Nc>
 __device__ __forceinline__ void real_pair(const float2* buf, const float2* rs, int k, float2& Xk,
                                           float2& Xm) {
   const float2 zk = buf[wfft::swz<Nc>(k)];
   const float2 zc = buf[wfft::swz<Nc>((Nc - k) & (Nc - 1))];
-  const float2 E = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y - zc.y));
-  const float2 O = make_float2(0.5f * (zk.y + zc.y), -0.5f * (zk.x - zc.x));
+  const float2 E = make_float2(zk.x + zc.x, zk.y - zc.y);
+  const float2 O = make_float2(zk.y + zc.y, zc.x - zk.x);
   const float2 WO = wfft::cmul(rs[k], O);
   Xk = wfft::add(E, WO);
   const float2 D = wfft::sub(E, WO);
@@ -105,10 +111,10 @@ __device__ __forceinline__ float target_log(float2 T) {
   return __builtin_amdgcn_logf(bin_mag(T, Ts, as) + kEps);
 }
 
-// One bin's loss share (added to acc) and gradient spectrum value, from the
+// One bin's |log difference| (added to acc) and gradient spectrum value, from the
 // render bin X and the target's lt = target_log(T).
-__device__ __forceinline__ float2 bin_grad(float2 X, float lt, double scale_d, float scale,
-                                           bool edge, bool want_grad, double& acc) {
+__device__ __forceinline__ float2 bin_grad(float2 X, float lt, float scale, bool edge,
+                                           bool want_grad, double& acc) {
   // hardware log2 and reciprocal (about 1 ulp each); G = sign(d) scale
   // X / (|X| (|X| + eps)) = sign(d) scale Xs / (as (|X| + eps)), whose
   // denominator stays a normal float32 for every bin
@@ -116,7 +122,7 @@ __device__ __forceinline__ float2 bin_grad(float2 X, float lt, double scale_d, f
   float as;
   const float ax = bin_mag(X, Xs, as);
   const float d = 0.69314718055994531f * (__builtin_amdgcn_logf(ax + kEps) - lt);
-  acc += scale_d * (double)fabsf(d);
+  acc += (double)fabsf(d);
   float2 G = make_float2(0.f, 0.f);
   if (want_grad && as > 0.0f && d != 0.0f) {
     const float gm = copysignf(scale, d) * __builtin_amdgcn_rcpf((ax + kEps) * as);
@@ -131,7 +137,7 @@ __device__ __forceinline__ float2 bin_grad(float2 X, float lt, double scale_d, f
 // (and gradient) with the target's log magnitudes read from a.tlog.
 template <int RES, int MODE>
 __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << RES>& sh, int64_t b,
-                                              int blk) {
+                                              int chunk) {
   constexpr int r = RES;
   constexpr int n = 512 << r;
   constexpr int Nc = n / 2;             // complex points per transform
@@ -141,7 +147,7 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
   constexpr int hop = n / 4;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
-  const int chunk = blk - a.chunk_base[r];
+  const int nch = a.chunk_base[r + 1] - a.chunk_base[r];
   const int F = a.F[r];
   const bool want_grad = MODE != 1 && a.wgrad != nullptr;
   // The scale is applied in float32 to the gradient and in float64 to the loss.
@@ -149,7 +155,7 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
   const float scale = (float)scale_d;
 
   // ---- tables of this resolution ----
-  for (int k = tid; k < n; k += kMrThreads) sh.win[k] = 0.5f - 0.5f * cospif(2.0f * (float)k / (float)n);
+  for (int k = tid; k < n; k += kMrThreads) sh.win[k] = 0.5f * (0.5f - 0.5f * cospif(2.0f * (float)k / (float)n));
   for (int k = tid; k <= Nc / 2; k += kMrThreads) {
     float sn, cs;
     sincospif(2.0f * (float)k / (float)n, &sn, &cs);
@@ -161,7 +167,6 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
 
   const int f_begin = chunk * kFramesPerBlock;
   const int f_end = min(F, f_begin + kFramesPerBlock);
-  const int nch = a.chunk_base[r + 1] - a.chunk_base[r];
   float* seg = want_grad ? a.wgrad + a.wbase[r] + ((int64_t)b * nch + chunk) * (kSegHops * hop)
                          : nullptr;
   float2* buf = sh.buf[wv];
@@ -227,51 +232,40 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
         float2 Xk, Xm;
         real_pair<Nc>(buf, sh.rs, k, Xk, Xm);
         if (q < QB) {
-          Hk[q] = bin_grad(Xk, Lk[q], scale_d, scale, k == 0, want_grad, acc);
-          Hm[q] = bin_grad(Xm, Lm[q], scale_d, scale, k == 0, want_grad, acc);   // bin Nc - k
+          Hk[q] = bin_grad(Xk, Lk[q], scale, k == 0, want_grad, acc);
+          Hm[q] = bin_grad(Xm, Lm[q], scale, k == 0, want_grad, acc);   // bin Nc - k
         } else {
           // bin Nc / 2, once per frame (lane 0)
           double a2 = 0.0;
-          Hk[q] = bin_grad(Xk, Lk[q], scale_d, scale, false, want_grad, a2);
+          Hk[q] = bin_grad(Xk, Lk[q], scale, false, want_grad, a2);
           if (lane == 0) acc += a2;
           Hm[q] = make_float2(0.f, 0.f);
         }
       }
       if (want_grad) {
-        // ---- H to LDS (slot k holds H_k; slot 0 holds (H_0, H_Nc), both real) ----
-        wfft::wave_fence();
-#pragma unroll
-        for (int q = 0; q < QB; ++q) {
-          const int k = lane + 64 * q;
-          if (k == 0) {
-            buf[wfft::swz<Nc>(0)] = make_float2(Hk[q].x, Hm[q].x);
-          } else {
-            buf[wfft::swz<Nc>(k)] = Hk[q];
-            buf[wfft::swz<Nc>(Nc - k)] = Hm[q];
-          }
-        }
-        if (lane == 0) buf[wfft::swz<Nc>(Nc / 2)] = Hk[QB];
-        wfft::wave_fence();
         // ---- inverse input: Y_m = (H_m + conj H_{Nc-m}) + i conj(W^m) (H_m - conj H_{Nc-m}) ----
+        // The lane has both H_k and H_{Nc-k}, so it forms Y_k and Y_{Nc-k}
+        // itself (for Nc - k the sum is conj A, the difference -conj D and W
+        // -conj W^k, so their product is conj(cd)); only Y goes through LDS.
+        wfft::wave_fence();
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-          const int m = lane + 64 * q;
-          float2 hk, hc;
-          if (m == 0) {
-            const float2 h0 = buf[wfft::swz<Nc>(0)];
-            hk = make_float2(h0.x, 0.f);
-            hc = make_float2(h0.y, 0.f);
-          } else {
-            hk = buf[wfft::swz<Nc>(m)];
-            const float2 t2 = buf[wfft::swz<Nc>(Nc - m)];
-            hc = make_float2(t2.x, -t2.y);
-          }
+        for (int q = 0; q <= QB; ++q) {
+          const int k = q < QB ? lane + 64 * q : Nc / 2;
+          const float2 hk = Hk[q];
+          const float2 hc = q < QB ? make_float2(Hm[q].x, -Hm[q].y) : make_float2(hk.x, -hk.y);
           const float2 A = wfft::add(hk, hc), D = wfft::sub(hk, hc);
-          // W^m = exp(-2 pi i m / n); for m > Nc / 2 from W^{Nc - m} = -conj(W^m)
-          const float2 wm = m <= Nc / 2 ? sh.rs[m] : make_float2(-sh.rs[Nc - m].x, sh.rs[Nc - m].y);
-          const float2 cd = wfft::cmulc(D, wm);        // conj(W^m) D
-          v[q] = make_float2(A.x - cd.y, A.y + cd.x);   // A + i (conj(W^m) D)
+          const float2 cd = wfft::cmulc(D, sh.rs[k]);   // conj(W^k) D
+          const float2 Yk = make_float2(A.x - cd.y, A.y + cd.x);   // A + i cd
+          if (q < QB) {
+            buf[wfft::swz<Nc>(k)] = Yk;
+            if (k > 0) buf[wfft::swz<Nc>(Nc - k)] = make_float2(A.x + cd.y, cd.x - A.y);
+          } else if (lane == 0) {
+            buf[wfft::swz<Nc>(k)] = Yk;
+          }
         }
+        wfft::wave_fence();
+#pragma unroll
+        for (int q = 0; q < P; ++q) v[q] = buf[wfft::swz<Nc>(lane + 64 * q)];
         wfft::wave_fft<Nc, false>(v, buf, sh.pt, lane);
       }
     }
@@ -279,21 +273,26 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
       __syncthreads();                  // the four frames' rows are in the buffers
       // ---- overlap-add: frame f0 + s contributes 0.5 w(o) y(o) at o = p - s hop ----
       const int p0 = (f0 - f_begin) * hop;           // block-relative start of frame f0
-      for (int p = tid; p < (kMrWaves - 1) * hop + n; p += kMrThreads) {
-        float g = 0.0f;
+      // two neighbouring samples a thread, which are one point of a buffer; a
+      // wavefront's 128 lie in one hop, so which frames cover them is uniform
+      for (int p = 2 * tid; p < (kMrWaves - 1) * hop + n; p += 2 * kMrThreads) {
+        const int hb = __builtin_amdgcn_readfirstlane(p / hop), po = p - hb * hop;
+        float2 g = make_float2(0.0f, 0.0f);
 #pragma unroll
         for (int s2 = 0; s2 < kMrWaves; ++s2) {
-          const int o = p - s2 * hop;
-          if (o >= 0 && o < n && f0 + s2 < f_end) {
-            const float2 yy = sh.buf[s2][wfft::swz<Nc>(o >> 1)];
-            g += 0.5f * sh.win[o] * ((o & 1) ? yy.y : yy.x);
+          if (hb >= s2 && hb - s2 < n / hop && f0 + s2 < f_end) {
+            const int m = ((hb - s2) * hop + po) >> 1;
+            const float2 yy = sh.buf[s2][wfft::swz<Nc>(m)];
+            const float2 w2 = *reinterpret_cast<const float2*>(&sh.win[2 * m]);
+            g.x += w2.x * yy.x;
+            g.y += w2.y * yy.y;
           }
         }
-        float* slotp = sh.ola + ((p0 + p) & (kOlaSlots - 1));
-        const float v2 = *slotp + g;
-        if (p < kMrWaves * hop) {                    // no later frame reaches it
-          seg[p0 + p] = v2;
-          *slotp = 0.0f;
+        float2* slotp = reinterpret_cast<float2*>(sh.ola + ((p0 + p) & (kOlaSlots - 1)));
+        const float2 v2 = wfft::add(*slotp, g);
+        if (hb < kMrWaves) {                         // no later frame reaches it
+          *reinterpret_cast<float2*>(seg + p0 + p) = v2;
+          *slotp = make_float2(0.0f, 0.0f);
         } else {
           *slotp = v2;
         }
@@ -316,7 +315,7 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
   if (tid == 0) {
     double s = 0.0;
     for (int w = 0; w < kMrWaves; ++w) s += sh.red[w];
-    a.partial[b * a.chunk_base[3] + blk] = s;
+    a.partial[b * a.chunk_base[3] + a.chunk_base[r] + chunk] = scale_d * s;
   }
 }
 
@@ -325,7 +324,7 @@ __device__ __forceinline__ void mrstft_frames(const MrArgs& a, MrShared<256 << R
 template <int RES, int MODE>
 __global__ void __launch_bounds__(kMrThreads) mrstft_frames_kernel(const MrArgs a) {
   __shared__ MrShared<256 << RES> sh;
-  mrstft_frames<RES, MODE>(a, sh, blockIdx.y, a.chunk_base[RES] + (int)blockIdx.x);
+  mrstft_frames<RES, MODE>(a, sh, blockIdx.y, (int)blockIdx.x);
 }
 
 // Log-mel features by FFT, workgroups of 4 wavefronts that take items of 16
@@ -364,7 +363,7 @@ struct MelShared {
   int cbase[kMelBands + 1];    // band b's chunks: cbase[b] .. cbase[b + 1] - 1
   int chunk[kMelChunksMax];    // first bin of chunk c
   float st[kMelBands][17];     // features of 16 frames, written out together
-  alignas(8) float win[2048];  // periodic Hann window
+  alignas(8) float win[2048];  // half the periodic Hann window (the real split's 1/2, exact)
   float2 rs[513];              // exp(-2 pi i k / 2048), k <= 512 (real split)
   float2 pt[wfft::pt_size<1024>()];   // FFT pass twiddles
 };
@@ -431,7 +430,7 @@ logmel_fft_kernel(const float* __restrict__ audio, const int64_t* __restrict__ o
     ms.rs[k] = make_float2(cs, -sn);
   }
   for (int k = tid; k < 2 * Nc; k += kMelThreads)
-    ms.win[k] = 0.5f - 0.5f * cospif(2.0f * (float)k / (float)(2 * Nc));
+    ms.win[k] = 0.5f * (0.5f - 0.5f * cospif(2.0f * (float)k / (float)(2 * Nc)));
   wfft::build_pass_twiddles<Nc>(ms.pt, tid, kMelThreads);
   __syncthreads();                      // band table and LDS tables written
   for (int e = tid; e < kMelBands * 4; e += kMelThreads) {
@@ -534,8 +533,8 @@ logmel_fft_kernel(const float* __restrict__ audio, const int64_t* __restrict__ o
         const int k = q < 8 ? lane + 64 * q : 512;
         const float2 zk = buf[wfft::swz<Nc>(k)];
         const float2 zc = buf[wfft::swz<Nc>((Nc - k) & (Nc - 1))];
-        const float2 E = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y - zc.y));
-        const float2 O = make_float2(0.5f * (zk.y + zc.y), -0.5f * (zk.x - zc.x));
+        const float2 E = make_float2(zk.x + zc.x, zk.y - zc.y);
+        const float2 O = make_float2(zk.y + zc.y, zc.x - zk.x);
         const float2 w = ms.rs[k];
         const float2 WO = wfft::cmul(w, O);
         pk[q] = pow_bf16(wfft::add(E, WO));
