@@ -26,7 +26,10 @@
 // d/d(normalised parameter).  Deterministic; no atomics.
 #include <math.h>
 
+#include <type_traits>
+
 #include "philox.h"
+#include "sine_table.h"
 #include "synth_internal.h"
 #include "voice_device.h"
 
@@ -43,6 +46,56 @@ enum {
   kNumRed
 };
 
+// sin and cos of 2 pi j / 256 from the quarter wave.
+__device__ __forceinline__ double2 sincos_entry(int j) {
+  const int r = j & 63, o = j >> 6;              // octet pair: quarter o, offset r
+  const double a = kSinT[r], b = kSinT[64 - r];  // sin, cos of the offset
+  switch (o) {
+    case 0: return make_double2(a, b);
+    case 1: return make_double2(b, -a);
+    case 2: return make_double2(-a, -b);
+    default: return make_double2(-b, a);
+  }
+}
+
+// sin and cos of 2 pi th in float64: th = n / 256 + d, |d| <= 1/512 (exact),
+// the table's sine and cosine at n mod 256 and, for a = 2 pi d (|a| <= 0.0123),
+// sin a to a^5 and cos a - 1 to a^6 (truncation 9e-18 and 2e-20), joined by
+// the addition theorems: 18 instructions after the reduction against 34 for
+// the two series on a quarter cycle, with the same rounding (2e-16).
+__device__ __forceinline__ void sincos_table(const double2* tab, double th, double& s, double& c) {
+  const double n = rint(256.0 * th);
+  const double a = fma(n, -1.0 / 256.0, th) * kTwoPi, a2 = a * a;
+  const double2 t = tab[(int)n & 255];
+  double p = fma(a2, kSeriesC[kSin5], kSeriesC[kSin3]);
+  const double sa = fma(p * a2, a, a);
+  p = fma(a2, kSeriesC[kCos6], kSeriesC[kCos4]);
+  const double ca = a2 * fma(a2, p, -0.5);       // cos a - 1
+  s = fma(t.y, sa, fma(t.x, ca, t.x));
+  c = fma(-t.x, sa, fma(t.y, ca, t.y));
+}
+
+// 2^y for y <= 0 by exp2_f64's method on 64 table points: |r| <= 1/128, so the
+// series runs to z^5 / 120 (truncation 4e-17).
+__device__ __forceinline__ double exp2_table(const double* tab, double y) {
+  y = fmax(y, -1100.0);
+  const double nd = rint(y * 64.0);
+  const int n = (int)nd;
+  const double z = fma(nd, -1.0 / 64.0, y) * kLn2;
+  double p = fma(z, kSeriesC[kExpC5], kSeriesC[kExpC4]);
+  p = fma(p, z, kSeriesC[kExpC3]);
+  p = fma(p, z, 0.5);
+  p = fma(p, z, 1.0);
+  p = fma(p, z, 1.0);
+  return ldexp(tab[n & 63] * p, n >> 6);
+}
+
+// Bound by float64 VALU issue at two wavefronts per SIMD: about 125
+// instructions a sample (205 with the series' sine and cosine, the weights,
+// ramps and products that follow from sums with and without the sample index
+// formed per sample, and the exponential's table in global memory); the render
+// adjoint of 256 voices of 4 s 710 -> 597 us.  LDS of 20.4 KB (noise as its 16-bit halves, 64 points
+// of the exponential) lets a CU hold the eight wavefronts the registers allow.
 template <int RPS>
 __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a,
                                                               const float* __restrict__ g_audio,
@@ -61,7 +114,11 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
   const float* gv = g_audio + b * N;
   double* rv = red + b * J * kNumRed;
   float* tg = tile;                 // g(n) of the pass
-  float* tgn = tile + kWave * h;    // g(n) * noise(n) of the pass
+  uint16_t* tn = reinterpret_cast<uint16_t*>(tile + kWave * h);   // 16-bit noise of the pass
+  __shared__ double2 sct[256];
+  __shared__ double e2t[64];
+  for (int j = lane; j < 256; j += kWave) sct[j] = sincos_entry(j);
+  for (int j = lane; j < 64; j += kWave) e2t[j] = kExp2T[4 * j];
 
   voice_setup(a, b, sh, lane);
   const double* v = sh.v;
@@ -83,12 +140,10 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
   const double m_hi = fmax(0.0, midi + v[71] + fmax(0.0, v[72]));
   const double f_hi = fmin(440.0 * exp2((m_hi - 69.0) / 12.0), sr / 2.0);
   const double Kd = 12000.0 / (f_hi * log10(f_hi));
-  const float shape = (float)v[74];
   const float cg = (float)(1.0 - v[74] / 2.0);
-  const double shape_d = v[74], cg2pi_d = (1.0 - v[74] / 2.0) * kTwoPi, L2d = v[76];
-  const double L1d_2pi = v[75] * kTwoPi;
-  constexpr double kM2Log2e = -2.0 * 1.4426950408889634;   // exp(-2|z|) = 2^(kM2Log2e |z|)
-  const float L1 = (float)v[75], L2 = (float)v[76], L3 = (float)v[77];
+  const double shape_d = v[74], L2cg2pi = v[76] * (1.0 - v[74] / 2.0) * kTwoPi;
+  const double L1d = v[75], L2d = v[76], L3d = v[77], L1d_2pi = v[75] * kTwoPi;
+  const double K2d = 2.0 * 1.4426950408889634 * Kd, K4d = 4.0 * Kd;   // exp(-2|z|) = 2^-(2 log2(e) |z|)
   const uint32_t glo = (uint32_t)g, ghi = (uint32_t)(g >> 32);
 
   int64_t c_start = 0;
@@ -111,11 +166,9 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
     control_stage<RPS, false>(a, sh, reinterpret_cast<double*>(tile), c, J, h, lane, y, yn);
     if (c < c_lo) continue;                      // slice starts later: only carries needed
     // unscaled VCA ramps of this lane's segment
-    const double a10_d = y[1], a1d_d = (yn[1] - y[1]) / qd;   // float64 ramp for the phase adjoint
-    const float a10 = (float)a10_d, a1d = (float)a1d_d;
-    const double a30_d = y[3], a3d_d = (yn[3] - y[3]) / qd;   // float64 ramp for the phase adjoint
-    const float a30 = (float)a30_d, a3d = (float)a3d_d;
-    const float a40 = (float)y[4], a4d = (float)((yn[4] - y[4]) / qd);
+    const double a10_d = y[1], a1d_d = (yn[1] - y[1]) / qd;
+    const double a30_d = y[3], a3d_d = (yn[3] - y[3]) / qd;
+    const double a40_d = y[4], a4d_d = (yn[4] - y[4]) / qd;
     __syncthreads();
 
     constexpr int segs_pp = kWave / RPS;
@@ -123,7 +176,7 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
                                                                     : kSegsPerChunk);
     const int npass = (nseg + segs_pp - 1) / segs_pp;
     for (int p = 0; p < npass; ++p) {
-      // ---- load pass: g and g * noise into LDS, 4 samples per lane ----
+      // ---- load pass: g and the noise halves into LDS, 4 samples per lane ----
       const int64_t pbase = (c * kSegsPerChunk + (int64_t)p * segs_pp) * q;
       int64_t cnt64 = (int64_t)((nseg - p * segs_pp) < segs_pp ? (nseg - p * segs_pp) : segs_pp) * q;
       if (cnt64 > N - pbase) cnt64 = N - pbase;
@@ -145,13 +198,8 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
             float gg[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) gg[e] = li + e < cnt ? gv[pbase + li + e] : 0.0f;
-            const float n0 = ((float)(wa & 0xFFFFu) - 32767.5f) * (1.0f / 32768.0f);
-            const float n1 = ((float)(wa >> 16) - 32767.5f) * (1.0f / 32768.0f);
-            const float n2 = ((float)(wb & 0xFFFFu) - 32767.5f) * (1.0f / 32768.0f);
-            const float n3 = ((float)(wb >> 16) - 32767.5f) * (1.0f / 32768.0f);
             *reinterpret_cast<float4*>(tg + li) = make_float4(gg[0], gg[1], gg[2], gg[3]);
-            *reinterpret_cast<float4*>(tgn + li) =
-                make_float4(gg[0] * n0, gg[1] * n1, gg[2] * n2, gg[3] * n3);
+            *reinterpret_cast<uint2*>(tn + li) = make_uint2(wa, wb);
           }
         }
       }
@@ -171,93 +219,111 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
           t2 += s2; s2 *= R2; i2 *= R2;
         }
       }
-      const float A10 = __shfl(a10, src), A1d = __shfl(a1d, src);
+      // VCA ramps at sample ks of the segment: x0 + ks xd.  In float64 with the
+      // phase adjoints' constant factors for the reason given below, in float32
+      // for the shape and gain sums.
       const double A10d = __shfl(a10_d, src), A1dd = __shfl(a1d_d, src);
-      const float A30 = __shfl(a30, src), A3d = __shfl(a3d, src);
       const double A30d = __shfl(a30_d, src), A3dd = __shfl(a3d_d, src);
-      const float A40 = __shfl(a40, src), A4d = __shfl(a4d, src);
-      double acc[kNumRed];
-#pragma unroll
-      for (int r = 0; r < kNumRed; ++r) acc[r] = 0.0;
-      // The amplitude-side sums (VCA rows, levels, shape, K) are accumulated in
-      // float32 over the run (at most q / RPS samples) and promoted once; the
-      // phase-adjoint sums stay float64.
-      float fa[kNumRed - kRA01];
-#pragma unroll
-      for (int r = 0; r < kNumRed - kRA01; ++r) fa[r] = 0.0f;
-      const double inv_q = 1.0 / qd;
+      const double A40d = __shfl(a40_d, src), A4dd = __shfl(a4d_d, src);
+      const double p10 = A10d * L1d_2pi, p1d = A1dd * L1d_2pi;
+      const double p30 = A30d * L2cg2pi, p3d = A3dd * L2cg2pi;
+      const float A30 = (float)A30d, A3d = (float)A3dd;
       double P1 = 0.0, P2 = 0.0;
+      // sums over the run of l = inc and ks l, of both times P (float64), and
+      // of d and ks d of the three amplitude terms, the shape and gain terms
+      // (float32 over at most q / RPS samples)
+      double c1 = 0.0, k1 = 0.0, e1 = 0.0, f1 = 0.0, c2 = 0.0, k2 = 0.0, e2 = 0.0, f2 = 0.0;
+      float s1 = 0.0f, w1 = 0.0f, s3 = 0.0f, w3 = 0.0f, s4 = 0.0f, w4 = 0.0f, fsh = 0.0f, fk = 0.0f;
       const int seg_valid = ls < nseg ? 1 : 0;
       // samples of this run that exist in the voice (the last segment may be partial)
       const int64_t run0 = (c * kSegsPerChunk + ls) * (int64_t)q + m * h;
       const int nlive = seg_valid ? (int)(N - run0 < h ? (N - run0 > 0 ? N - run0 : 0) : h) : 0;
-      for (int k = 0; k < h; ++k) {
-        const int ks = m * h + k;                  // sample index within the segment
-        const double live = k < nlive ? 1.0 : 0.0;
-        const float kf = (float)ks;
-        const double wt1 = (double)ks * inv_q, wt0 = 1.0 - wt1;
-        const float wt1f = (float)ks * (float)inv_q, wt0f = 1.0f - wt1f;
-        const float gk = seg_valid ? tg[lane * h + k] : 0.0f;
-        const float gnk = seg_valid ? tgn[lane * h + k] : 0.0f;
-        const float a1 = fmaf(kf, A1d, A10), a3 = fmaf(kf, A3d, A30), a4 = fmaf(kf, A4d, A40);
-        // sine VCO (its phase adjoint in float64 for the reason given below)
-        const float r1f = (float)(t1 - rint(t1));
-        const float x1 = __builtin_amdgcn_sinf(r1f);
-        const double dth1 = (double)gk * L1d_2pi * fma((double)ks, A1dd, A10d) * cos_cycles_f64(t1);
-        // square-saw VCO: T = tanh(K s), sech^2 = 4e/(1+e)^2 with e = exp(-2|K s|).
-        // Its phase adjoint is a sum over the voice of terms of both signs that
-        // the tanh edge scales by up to 2 pi K; for pitch parameters the sum can
-        // be 1e6 times smaller than the sum of its magnitudes, so float32
-        // rounding of the terms (the hardware sine and exponential, the VCA
-        // ramp) would dominate it.  The term is evaluated in float64.
-        double s2, c2;
-        sincos_cycles_f64(t2, s2, c2);
-        const double zd = Kd * s2;
-        const double e = exp2_f64(kM2Log2e * fabs(zd));
-        const double de = 1.0 + e;
-        double ri = __builtin_amdgcn_rcp(de);
-        ri = fma(fma(-de, ri, 1.0), ri, ri);
-        ri = fma(fma(-de, ri, 1.0), ri, ri);
-        const double Td = copysign((1.0 - e) * ri, zd);
-        const double sech2 = 4.0 * e * ri * ri;
-        const double Qd = fma(shape_d, c2, 1.0);
-        const double gl2a3d = (double)gk * L2d * fma((double)ks, A3dd, A30d);
-        const double dth2 = gl2a3d * cg2pi_d * (sech2 * Kd * c2 * Qd - Td * shape_d * s2);
-        const float s2f = (float)s2, c2f = (float)c2, T = (float)Td, Q = (float)Qd;
-        const float x2 = cg * T * Q;
-        const float gl2a3 = gk * L2 * a3;
-        // phase-adjoint reductions (float64)
-        P1 += dth1;
-        P2 += dth2;
-        const double l1 = live * i1, l2 = live * i2;
-        acc[kRC01] += wt0 * l1;
-        acc[kRC11] += wt1 * l1;
-        acc[kRE01] += wt0 * l1 * P1;
-        acc[kRE11] += wt1 * l1 * P1;
-        acc[kRC02] += wt0 * l2;
-        acc[kRC12] += wt1 * l2;
-        acc[kRE02] += wt0 * l2 * P2;
-        acc[kRE12] += wt1 * l2 * P2;
-        // VCA rows (transposed upsampling weights), levels, shape, K
-        const float d1 = gk * L1 * x1, d3 = gk * L2 * x2, d4 = L3 * gnk;
-        fa[kRA01 - kRA01] = fmaf(wt0f, d1, fa[kRA01 - kRA01]);
-        fa[kRA11 - kRA01] = fmaf(wt1f, d1, fa[kRA11 - kRA01]);
-        fa[kRA03 - kRA01] = fmaf(wt0f, d3, fa[kRA03 - kRA01]);
-        fa[kRA13 - kRA01] = fmaf(wt1f, d3, fa[kRA13 - kRA01]);
-        fa[kRA04 - kRA01] = fmaf(wt0f, d4, fa[kRA04 - kRA01]);
-        fa[kRA14 - kRA01] = fmaf(wt1f, d4, fa[kRA14 - kRA01]);
-        fa[kRL1 - kRA01] += gk * x1 * a1;
-        fa[kRL2 - kRA01] += gk * x2 * a3;
-        fa[kRL3 - kRA01] += gnk * a4;
-        fa[kRShape - kRA01] += gl2a3 * (cg * T * c2f - 0.5f * T * Q);
-        fa[kRK - kRA01] += gl2a3 * cg * (float)sech2 * s2f * Q;
-        t1 += i1; i1 *= r1;
-        t2 += i2; i2 *= r2;
-      }
+      const float* tgl = tg + lane * h;
+      const uint16_t* tnl = tn + lane * h;
+      auto run = [&](auto whole) {
+        double kd = (double)(m * h);                 // sample index within the segment
+        float kf = (float)(m * h);
+#pragma unroll 1
+        for (int k = 0; k < h; ++k) {
+          const float gk = tgl[k];                   // 0 past the voice's end
+          const float nn = (float)tnl[k] - 32767.5f;
+          const double gd = (double)gk;
+          double sn1, cs1, sn2, cs2;
+          sincos_table(sct, t1, sn1, cs1);
+          sincos_table(sct, t2, sn2, cs2);
+          // Phase adjoints.  Square-saw: T = tanh(K s), sech^2 = 4e/(1+e)^2 with
+          // e = exp(-2|K s|).  Its phase adjoint is a sum over the voice of
+          // terms of both signs that the tanh edge scales by up to 2 pi K; for
+          // pitch parameters the sum can be 1e6 times smaller than the sum of
+          // its magnitudes, so float32 rounding of the terms (the hardware sine
+          // and exponential, the VCA ramp) would dominate it.  The term is
+          // evaluated in float64, and the sine VCO's alike.
+          const double e = exp2_table(e2t, -fabs(K2d * sn2));
+          const double de = 1.0 + e;
+          double ri = __builtin_amdgcn_rcp(de);
+          ri = fma(fma(-de, ri, 1.0), ri, ri);
+          ri = fma(fma(-de, ri, 1.0), ri, ri);
+          const double T = copysign((1.0 - e) * ri, sn2);
+          const double er = e * ri * ri;             // sech^2 / 4
+          const double Q = fma(shape_d, cs2, 1.0);
+          P1 += gd * fma(kd, p1d, p10) * cs1;
+          P2 += gd * fma(kd, p3d, p30) * fma(er * cs2 * Q, K4d, -(shape_d * sn2) * T);
+          const double l1 = whole.value || k < nlive ? i1 : 0.0;
+          const double l2 = whole.value || k < nlive ? i2 : 0.0;
+          const double m1 = kd * l1, m2 = kd * l2;
+          c1 += l1;
+          k1 += m1;
+          e1 = fma(l1, P1, e1);
+          f1 = fma(m1, P1, f1);
+          c2 += l2;
+          k2 += m2;
+          e2 = fma(l2, P2, e2);
+          f2 = fma(m2, P2, f2);
+          // amplitude side
+          const float x2 = (float)(T * Q), tc = (float)(T * cs2), ek = (float)(er * sn2 * Q);
+          const float d1 = gk * (float)sn1, d3 = gk * x2, d4 = gk * nn;
+          const float ga3 = gk * fmaf(kf, A3d, A30);
+          s1 += d1;
+          w1 = fmaf(kf, d1, w1);
+          s3 += d3;
+          w3 = fmaf(kf, d3, w3);
+          s4 += d4;
+          w4 = fmaf(kf, d4, w4);
+          fsh = fmaf(ga3, fmaf(cg, tc, -0.5f * x2), fsh);
+          fk = fmaf(ga3, ek, fk);
+          t1 += i1; i1 *= r1;
+          t2 += i2; i2 *= r2;
+          kd += 1.0;
+          kf += 1.0f;
+        }
+      };
+      if (__all(nlive == h || !seg_valid)) run(std::true_type{});   // invalid lanes are not used
+      else run(std::false_type{});
+      // the sums with the upsampling weights 1 - ks / q and ks / q
+      const double inv_q = 1.0 / qd;
+      double acc[kNumRed];
       acc[kRD1] = P1;
+      acc[kRC11] = k1 * inv_q;
+      acc[kRC01] = c1 - acc[kRC11];
+      acc[kRE11] = f1 * inv_q;
+      acc[kRE01] = e1 - acc[kRE11];
       acc[kRD2] = P2;
-#pragma unroll
-      for (int r = kRA01; r < kNumRed; ++r) acc[r] = (double)fa[r - kRA01];
+      acc[kRC12] = k2 * inv_q;
+      acc[kRC02] = c2 - acc[kRC12];
+      acc[kRE12] = f2 * inv_q;
+      acc[kRE02] = e2 - acc[kRE12];
+      const double L2cg = L2d * (double)cg, L3n = L3d * (1.0 / 32768.0);
+      acc[kRA11] = L1d * w1 * inv_q;
+      acc[kRA01] = L1d * s1 - acc[kRA11];
+      acc[kRA13] = L2cg * w3 * inv_q;
+      acc[kRA03] = L2cg * s3 - acc[kRA13];
+      acc[kRA14] = L3n * w4 * inv_q;
+      acc[kRA04] = L3n * s4 - acc[kRA14];
+      acc[kRL1] = A10d * s1 + A1dd * w1;
+      acc[kRL2] = (double)cg * (A30d * s3 + A3dd * w3);
+      acc[kRL3] = (A40d * s4 + A4dd * w4) * (1.0 / 32768.0);
+      acc[kRShape] = L2d * fsh;
+      acc[kRK] = 4.0 * L2cg * fk;
       // combine the RPS runs of each segment: E += P_before * C, then sums
       if (RPS > 1) {
         const int gb = lane & ~(RPS - 1);          // first lane of this segment's group
@@ -738,7 +804,7 @@ __global__ void __launch_bounds__(kWave) adjoint_params_kernel(const RenderArgs 
 template <int RPS>
 hipError_t launch_adjoint_rps(const RenderArgs& a, const float* g, double* red, float* gp,
                               hipStream_t s) {
-  size_t shmem = (size_t)2 * kWave * (a.q / RPS) * sizeof(float);
+  size_t shmem = (size_t)kWave * (a.q / RPS) * (sizeof(float) + sizeof(uint16_t));
   if (shmem < 8 * kWave * sizeof(double)) shmem = 8 * kWave * sizeof(double);
   hipLaunchKernelGGL((adjoint_audio_kernel<RPS>), dim3((unsigned)(a.batch * a.slices)), dim3(kWave),
                      shmem, s, a, g, red);

@@ -11,7 +11,12 @@ arithmetic", ACM TOMS 15(2), 1989, and its logarithm counterpart, ACM TOMS
 (the log2 reduction takes m in [1/sqrt 2, sqrt 2), so j = rint(256 (m - 1))
 lies in -75 .. 106).
 
-Run from this directory: python gen_series_tables.py (build.py runs it).
+and sine_table.h, the quarter wave of the adjoint's table-driven sine and
+cosine (the same reduction with the addition theorems):
+
+  SIN_T[j]       = sin(2 pi j / 256),    j = 0 .. 64
+
+Run from this directory: python gen_series_tables.py.
 """
 from decimal import Decimal, getcontext
 import os
@@ -30,6 +35,27 @@ def tables():
     log2 = [(1 + Decimal(j) / 256).ln() / LN2 for j in range(LOG_J0, LOG_J1 + 1)]
     invc = [1 / (1 + Decimal(j) / 256) for j in range(LOG_J0, LOG_J1 + 1)]
     return exp2, log2, invc
+
+
+def sine_table():
+    # pi by Machin's formula, sin by its Taylor series, both in 60 digits
+    def atan_inv(n):
+        t, k, tot = Decimal(1) / n, 1, Decimal(0)
+        while abs(t) > Decimal(10) ** -58:
+            tot += t / k if k % 4 == 1 else -t / k
+            t /= n * n
+            k += 2
+        return tot
+    pi = 4 * (4 * atan_inv(5) - atan_inv(239))
+
+    def sin(x):
+        t, k, tot = x, 1, Decimal(0)
+        while abs(t) > Decimal(10) ** -58:
+            tot += t
+            t = -t * x * x / ((k + 1) * (k + 2))
+            k += 2
+        return tot
+    return [sin(2 * pi * j / 256) for j in range(65)]
 
 
 def main(path=None):
@@ -54,5 +80,18 @@ def main(path=None):
     return path
 
 
+def main_sine(path=None):
+    path = path or os.path.join(os.path.dirname(os.path.abspath(__file__)), "sine_table.h")
+    vals = [hexd(v) for v in sine_table()]
+    body = ",\n".join("    " + ", ".join(vals[i:i + 4]) for i in range(0, len(vals), 4))
+    with open(path, "w") as f:
+        f.write("// Generated by gen_series_tables.py: sin(2 pi j / 256), j = 0 .. 64, correctly\n"
+                "// rounded.\n#pragma once\n\nnamespace synth {\nnamespace voice {\n\n"
+                f"static __device__ double kSinT[{len(vals)}] = {{\n{body}}};\n"
+                "\n}  // namespace voice\n}  // namespace synth\n")
+    return path
+
+
 if __name__ == "__main__":
     print(main())
+    print(main_sine())

@@ -34,6 +34,10 @@ namespace {
 
 using namespace voice;
 
+struct RenderShared : VoiceShared {
+  float2 namp[kWave];          // per segment of the chunk: noise VCA (start, slope) * level * 2^-15
+};
+
 // Zero out[z0, z1) with all 64 lanes (z0 a multiple of 4).
 __device__ void zero_fill(float* out, int64_t z0, int64_t z1, int lane, bool aligned) {
   if (z1 <= z0) return;
@@ -98,7 +102,7 @@ __device__ __forceinline__ void noise_group(float* out, const float* tile, int g
 // Slice `slice` of voice b; of its passes those p with p mod a.pass_split ==
 // sub, and that share of its silent samples.
 template <int RPS, bool CLAMP>
-__device__ void render_item(const RenderArgs& a, int64_t b, int slice, int sub, VoiceShared& sh,
+__device__ void render_item(const RenderArgs& a, int64_t b, int slice, int sub, RenderShared& sh,
                             float* tile) {
   const int lane = threadIdx.x;
   const int q = a.q;
@@ -271,7 +275,7 @@ __device__ void render_item(const RenderArgs& a, int64_t b, int slice, int sub, 
 
 template <int RPS, bool CLAMP>
 __global__ void __launch_bounds__(kWave) render_kernel(const RenderArgs a) {
-  __shared__ VoiceShared sh;
+  __shared__ RenderShared sh;
   extern __shared__ __align__(16) float tile[];
   const int per = a.slices * a.pass_split;     // workgroups per voice
   const int64_t nitems = a.batch * per;

@@ -129,17 +129,6 @@ __device__ __forceinline__ void sincos_cycles_f64(double th, double& s, double& 
   c = sg * pc;
 }
 
-// cos(2 pi th) in float64 by the reduction and series of sincos_cycles_f64.
-__device__ __forceinline__ double cos_cycles_f64(double th) {
-  const double n = rint(2.0 * th);
-  const double a = fma(-0.5, n, th) * kTwoPi, a2 = a * a;
-  double pc = kSeriesC[kCos22];
-#pragma unroll
-  for (int k = kCos20; k >= kCos2; --k) pc = fma(pc, a2, kSeriesC[k]);
-  pc = fma(pc, a2, 1.0);
-  return (((int)n) & 1) ? -pc : pc;
-}
-
 // x^e for x in [0, 1] (0^e = 0, 1^e = 1 without evaluating exp2/log2); in
 // (0, 1) within about 1e-13 relative of the correctly rounded power.
 __device__ __forceinline__ double pow01(double x, double e) {
@@ -251,7 +240,6 @@ struct VoiceShared {
                                       // start increment, per-sample ratio, first-run sum,
                                       // per-run ratio
   double carry[4];             // phase carries (cycles): LFO 1, LFO 2, VCO 1, VCO 2
-  float2 namp[kWave];          // per segment of the chunk: noise VCA (start, slope) * level * 2^-15
 };
 
 // Maps voice b's parameters into sh.v, fills the derived constants sh.d and
