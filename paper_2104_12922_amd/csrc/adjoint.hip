@@ -90,6 +90,41 @@ __device__ __forceinline__ double exp2_table(const double* tab, double y) {
   return ldexp(tab[n & 63] * p, n >> 6);
 }
 
+// Per chunk of a voice, after the segment sums red [batch][21][J]: its four
+// sums over the carries it started from (read by the audio workgroup that
+// starts there and by nobody after), and what the control-rate pass adds up.
+struct CtlArgs {
+  double* sums;      // [batch][chunks][4]: LFO 1, 2 phases at the chunk's start; D1, D2 over it
+  double* gpart;     // [batch][chunks][kPartOut]: adjoint sums of the chunk, the first kPartOut
+  int64_t nchunks;
+};
+
+// x of the lane that the data-parallel control CTRL names.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0u, (uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0u, (uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double wave_sum(double x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+  return x;
+}
+
+// First chunk from which a voice is silent: every envelope is 0 with zero
+// derivative from control sample floor(note-off + longest release) + 2 on, so
+// no parameter sees the samples there.
+__device__ __forceinline__ int64_t silent_chunk(const double* v, double rc) {
+  double jsil = 0.0;
+  for (int k = 0; k < 6; ++k) jsil = fmax(jsil, v[1] * rc + v[2 + 5 * k + 3] * rc);
+  jsil = fmin(jsil, 9.0e15);
+  const int64_t js = (int64_t)floor(jsil) + 2;
+  return (js + kSegsPerChunk - 1) / kSegsPerChunk;
+}
+
 // Bound by float64 VALU issue at two wavefronts per SIMD: about 125
 // instructions a sample (205 with the series' sine and cosine, the weights,
 // ramps and products that follow from sums with and without the sample index
@@ -97,9 +132,10 @@ __device__ __forceinline__ double exp2_table(const double* tab, double y) {
 // adjoint of 256 voices of 4 s 710 -> 597 us.  LDS of 20.4 KB (noise as its 16-bit halves, 64 points
 // of the exponential) lets a CU hold the eight wavefronts the registers allow.
 template <int RPS>
-__global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a,
+__global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArgs a,
                                                               const float* __restrict__ g_audio,
-                                                              double* __restrict__ red) {
+                                                              double* __restrict__ red,
+                                                              CtlArgs ctl) {
   __shared__ VoiceShared sh;
   extern __shared__ __align__(16) float tile[];
   const int lane = threadIdx.x;
@@ -113,6 +149,7 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
   const uint64_t g = a.voice_ids ? a.voice_ids[b] : a.first_g + (uint64_t)b;
   const float* gv = g_audio + b * N;
   double* rv = red + b * J * kNumRed;
+  double* cs = ctl.sums + b * ctl.nchunks * 4;
   float* tg = tile;                 // g(n) of the pass
   uint16_t* tn = reinterpret_cast<uint16_t*>(tile + kWave * h);   // 16-bit noise of the pass
   __shared__ double2 sct[256];
@@ -122,14 +159,9 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
 
   voice_setup(a, b, sh, lane);
   const double* v = sh.v;
-  const double rc = a.rc, sr = a.sr;
-  const double note_off = v[1] * rc;
-  double jsil = 0.0;
-  for (int k = 0; k < 6; ++k) jsil = fmax(jsil, note_off + v[2 + 5 * k + 3] * rc);
-  jsil = fmin(jsil, 9.0e15);
-  const int64_t js = (int64_t)floor(jsil) + 2;
-  const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
-  const int64_t c_sil = (js + kSegsPerChunk - 1) / kSegsPerChunk;
+  const double sr = a.sr;
+  const int64_t nchunks = ctl.nchunks;
+  const int64_t c_sil = silent_chunk(v, a.rc);
   // this workgroup's chunks (a voice may be split over several workgroups;
   // the carries at its first chunk are precomputed, or the earlier chunks
   // are walked through the control stage only)
@@ -155,14 +187,14 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
   }
   for (int64_t c = c_start; c < c_hi; ++c) {
     if (c >= c_sil) {
-      // exactly silent from here on: every reduction is zero (the envelopes are
-      // 0 with zero derivative, so no parameter sees these samples)
-      const int64_t s0 = (c > c_lo ? c : c_lo) * kSegsPerChunk;
-      const int64_t s1 = c_hi * kSegsPerChunk < J ? c_hi * kSegsPerChunk : J;
-      for (int64_t i = lane; i < (s1 - s0) * kNumRed; i += kWave) rv[s0 * kNumRed + i] = 0.0;
+      // exactly silent from here on: no segment sums are read, only the chunks'
+      const int64_t s0 = c > c_lo ? c : c_lo;
+      for (int64_t i = lane; i < (c_hi - s0) * 4; i += kWave) cs[s0 * 4 + i] = 0.0;
       break;
     }
     double y[5], yn[5];
+    if (c >= c_lo && lane < 2) cs[c * 4 + lane] = sh.carry[lane];   // at the chunk's start
+    __syncthreads();
     control_stage<RPS, false>(a, sh, reinterpret_cast<double*>(tile), c, J, h, lane, y, yn);
     if (c < c_lo) continue;                      // slice starts later: only carries needed
     // unscaled VCA ramps of this lane's segment
@@ -175,6 +207,7 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
     const int nseg = (int)((J - c * kSegsPerChunk) < kSegsPerChunk ? (J - c * kSegsPerChunk)
                                                                     : kSegsPerChunk);
     const int npass = (nseg + segs_pp - 1) / segs_pp;
+    double D1c = 0.0, D2c = 0.0;
     for (int p = 0; p < npass; ++p) {
       // ---- load pass: g and the noise halves into LDS, 4 samples per lane ----
       const int64_t pbase = (c * kSegsPerChunk + (int64_t)p * segs_pp) * q;
@@ -325,42 +358,105 @@ __global__ void __launch_bounds__(kWave) adjoint_audio_kernel(const RenderArgs a
       acc[kRShape] = L2d * fsh;
       acc[kRK] = 4.0 * L2cg * fk;
       // combine the RPS runs of each segment: E += P_before * C, then sums
-      if (RPS > 1) {
-        const int gb = lane & ~(RPS - 1);          // first lane of this segment's group
-        double pb1 = 0.0, pb2 = 0.0;
-        for (int mm = 0; mm < RPS; ++mm) {
-          const double d1v = __shfl(P1, gb + mm), d2v = __shfl(P2, gb + mm);
-          if (mm < m) { pb1 += d1v; pb2 += d2v; }
-        }
+      if constexpr (RPS == 4) {
+        // lanes 4i .. 4i + 3: prefix and sums by quad permutations
+        auto before = [&](double P) {
+          double t = dpp_f64<0x90>(P);               // lanes 0, 0, 1, 2
+          double i2 = P + (m >= 1 ? t : 0.0);
+          t = dpp_f64<0x44>(i2);                     // lanes 0, 1, 0, 1
+          i2 += m >= 2 ? t : 0.0;
+          t = dpp_f64<0x90>(i2);
+          return m >= 1 ? t : 0.0;
+        };
+        const double pb1 = before(P1), pb2 = before(P2);
         acc[kRE01] += pb1 * acc[kRC01];
         acc[kRE11] += pb1 * acc[kRC11];
         acc[kRE02] += pb2 * acc[kRC02];
         acc[kRE12] += pb2 * acc[kRC12];
 #pragma unroll
         for (int r = 0; r < kNumRed; ++r) {
-          double tot = 0.0;
-          for (int mm = 0; mm < RPS; ++mm) tot += __shfl(acc[r], gb + mm);
-          acc[r] = tot;
+          double t = acc[r] + dpp_f64<0xB1>(acc[r]); // lanes 1, 0, 3, 2
+          acc[r] = t + dpp_f64<0x4E>(t);             // lanes 2, 3, 0, 1
         }
+      } else {
+        static_assert(RPS == 1, "one or four runs per segment");
       }
       const int64_t sglob = c * kSegsPerChunk + ls;
       if (m == 0 && ls < nseg) {
 #pragma unroll
-        for (int r = 0; r < kNumRed; ++r) rv[sglob * kNumRed + r] = acc[r];
+        for (int r = 0; r < kNumRed; ++r) rv[r * J + sglob] = acc[r];
+        D1c += acc[kRD1];
+        D2c += acc[kRD2];
       }
       __syncthreads();
+    }
+    D1c = wave_sum(D1c);
+    D2c = wave_sum(D2c);
+    if (lane == 0) {
+      cs[c * 4 + 2] = D1c;
+      cs[c * 4 + 3] = D2c;
     }
   }
 }
 
-// Per-lane parameter accumulators; rows padded by one double so that the
-// final per-parameter sums over lanes (lane p reads row p) hit distinct banks.
-constexpr int kAccRow = kWave + 1;
+// A chunk's adjoint sums: the 78 parameters', then for each LFO eight factors
+// and its phase-adjoint sum.  The phase adjoint of an LFO at control sample k
+// is summed over all later samples of the voice; what lies in later chunks
+// enters the chunk's adjoints as one number per LFO, so its factor in the rate
+// ADSR's A, D, S, R, alpha, note-off, the rate and the depth is summed as well
+// and applied when the chunks are joined.
+enum { kSumTail = kNumParams, kSumDph = kSumTail + 16, kNumSums = kSumDph + 2, kPartOut = 84 };
 
-// Adds x to lane's accumulator of parameter p (gradient pass only).
-template <bool G>
-__device__ __forceinline__ void gadd(double (*g)[kAccRow], int p, int lane, double x) {
-  if constexpr (G) g[p][lane] += x;
+// The sums from kPartOut on go into the chunk's own part of the segment sums:
+// its first segment's column of the rows that only the chunk itself reads, by
+// then in registers (a workspace of the size that callers hold has no more room).
+__device__ __forceinline__ int64_t tail_index(int n, int64_t c, int64_t J) {
+  const int e = n - kPartOut;
+  const int r = e < 2   ? kRC01 + 2 * e
+                : e < 4 ? kRC02 + 2 * (e - 2)
+                : e < 7 ? kRA01 + 2 * (e - 4)
+                        : kRL1 + e - 7;
+  return r * J + c * kSegsPerChunk;
+}
+static_assert(kNumSums - kPartOut == 12 && kRE01 == kRC01 + 2 && kRE02 == kRC02 + 2 &&
+                  kRA04 == kRA01 + 4 && kRK == kRL1 + 4, "rows read by one chunk only");
+
+// Rows of a wavefront's partial sums, in the order in which they come: eight per
+// ADSR k (A, D, S, R, alpha, the factors of alpha and note-off), four factors
+// (A, D, S, R) per LFO, twelve per LFO (its eight parameters, the factors of
+// rate and depth, the phase-adjoint sum), the mixer, the parameters 68 .. 77,
+// midi and note-off.
+enum {
+  kRowEnv = 0, kRowTail = 48, kRowLfo = 56, kRowMix = 80, kRowOsc = 100, kRowMidi = 110,
+  kRowOff = 112, kNumRows = 116
+};
+
+__device__ __forceinline__ int sum_row(int n) {
+  if (n == 0) return kRowMidi;
+  if (n == 1) return kRowOff;
+  if (n < 32) return kRowEnv + 8 * ((n - 2) / 5) + (n - 2) % 5;
+  if (n < 48) return kRowLfo + 12 * ((n - 32) / 8) + (n - 32) % 8;
+  if (n < 68) return kRowMix + n - 48;
+  if (n < kSumTail) return kRowOsc + n - 68;
+  if (n >= kSumDph) return kRowLfo + 12 * (n - kSumDph) + 10;
+  const int i = (n - kSumTail) / 8, r = (n - kSumTail) % 8;
+  return r < 4 ? kRowTail + 4 * i + r : r < 6 ? kRowEnv + 8 * (2 + 2 * i) + 1 + r : kRowLfo + 12 * i + 2 + r;
+}
+
+// Four values per lane -> part[row + (lane & 3)][lane / 16]: the sum of value
+// lane & 3 over the lane's row of sixteen.  Each of the first two steps halves
+// the values a lane holds (27 instructions for four sums; four steps for each
+// value by itself take 48).
+constexpr int kPartRow = 5;
+__device__ __forceinline__ void emit4(double (*part)[kPartRow], int row, int lane, double x0,
+                                      double x1, double x2, double x3) {
+  const bool o1 = lane & 1, o2 = lane & 2;
+  const double a = (o1 ? x1 : x0) + dpp_f64<0xB1>(o1 ? x0 : x1);   // quad_perm 1, 0, 3, 2
+  const double b = (o1 ? x3 : x2) + dpp_f64<0xB1>(o1 ? x2 : x3);
+  double s = (o2 ? b : a) + dpp_f64<0x4E>(o2 ? a : b);             // quad_perm 2, 3, 0, 1
+  s += dpp_f64<0x128>(s);                                          // row_ror 8
+  s += dpp_f64<0x124>(s);                                          // row_ror 4
+  if ((lane & 15) < 4) part[row + (lane & 3)][lane >> 4] = s;
 }
 
 // Reverse exclusive scan over lanes: sum of x over lanes l' > l.
@@ -375,35 +471,20 @@ __device__ __forceinline__ double wave_rev_excl_scan(double x, int lane) {
   return lane == kWave - 1 ? 0.0 : ex;
 }
 
-// float64 ADSR with the pieces its adjoint needs.
-struct EnvEval {
-  double att, dec, rel, Pa, Pd, Pr, M, env;
-};
-
-__device__ __forceinline__ EnvEval env_eval(const double* dv, int k, double jd, double note_off) {
-  EnvEval E;
-  const double A = dv[kEnvA + k], D = dv[kEnvD + k], R = dv[kEnvR + k];
-  const double S = dv[kEnvS + k], al = dv[kEnvAlpha + k];
-  E.att = ramp(jd, 0.0, A, dv[kEnvInvA + k]);
-  E.dec = ramp(jd, A, D, dv[kEnvInvD + k]);
-  E.rel = ramp(jd, note_off, R, dv[kEnvInvR + k]);
-  E.Pa = pow01(E.att, al);
-  E.Pd = pow01(1.0 - E.dec, al);
-  E.Pr = pow01(1.0 - E.rel, al);
-  E.M = S + (1.0 - S) * E.Pd;
-  E.env = E.Pa * E.M * E.Pr;
-  return E;
-}
-
-// d/dx x^alpha and d/dalpha x^alpha for x in (0, 1] (0 for x <= 0, as the
-// oracle's masked power).
-__device__ __forceinline__ void pow01_grad(double x, double al, double P, double& dx, double& dal) {
-  if (x > 0.0) {
+// x^alpha for x in [0, 1] as pow01 with its derivatives d/dx and d/dalpha (0
+// for x <= 0, as the oracle's masked power).
+__device__ __forceinline__ void pow01_grad(double x, double al, double& P, double& dx, double& dal) {
+  P = 0.0;
+  dx = 0.0;
+  dal = 0.0;
+  if (x >= 1.0) {
+    P = 1.0;
+    dx = al;
+  } else if (x > 0.0) {
+    const double l2 = log2_f64(x);
+    P = exp2_f64(al * l2);
     dx = al * P / x;
-    dal = P * log(x);
-  } else {
-    dx = 0.0;
-    dal = 0.0;
+    dal = P * (l2 * kLn2);
   }
 }
 
@@ -415,86 +496,84 @@ __device__ __forceinline__ bool ramp_live(double jd, double s, double L, double 
   return r >= 0.0 && r <= 1.0;
 }
 
-// Control-rate adjoint of chunk c of a voice: control samples j = 62c ..
-// 62c + 61 on lanes 1..62 (lane l <-> j = 62c - 1 + l); lane 0 carries
-// segment 62c - 1, whose right-end adjoint lands on lane 1.  The chunk needs
-// from the others only Gend1/2 (the phase adjoints D of all later segments),
-// lc (both LFO phases at control sample 62c) and, for the parameter
-// adjoints, Lsuf (both LFOs' phase adjoints summed over all later control
-// samples).  dph_tot receives this chunk's LFO phase-adjoint sums; with GRADS
-// the chunk's parameter adjoints are added to gacc[p][lane].
-template <bool GRADS>
-__device__ __forceinline__ void control_chunk(const RenderArgs& a, const VoiceShared& vs,
-                                              double (*gacc)[kAccRow], const double* rv, int64_t c,
-                                              int64_t J, int lane, double Gend1, double Gend2,
-                                              const double* lc, const double* Lsuf,
-                                              double* dph_tot) {
-  const double* v = vs.v;
-  const double* dv = vs.d;
+// The control-rate adjoint, chunk-parallel: one wavefront per (voice, chunk),
+// control samples j = 62c .. 62c + 61 on lanes 1 .. 62 (lane l <-> j = 62c - 1
+// + l); lane 0 carries segment 62c - 1, whose right-end adjoint lands on lane
+// 1.  From the other chunks it needs the phase adjoints D of all later segments
+// and both LFO phases at control sample 62c, both left by the audio pass.
+//
+// Bound by float64 issue (about 3000 instructions a chunk).  Two earlier
+// passes over the chunks (LFO phase totals, then the LFOs' phase adjoints) are
+// gone, the latter by the factors above, and the per-lane accumulators in LDS
+// (47.6 KB, three wavefronts per CU) by sums across lanes as the values come:
+// 256 voices of 4 s @TIME@.  The ADSRs are evaluated twice,
+// once for their values and once with their logarithms for the derivatives,
+// in loops over the six: kept in registers they cost the occupancy.
+struct GradShared {
+  VoiceShared vs;
+  double part[kNumRows][kPartRow];
+};
+
+__global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const RenderArgs a,
+                                                                      double* red, CtlArgs t) {
+  __shared__ GradShared S;
+  const int lane = threadIdx.x;
+  const int64_t b = blockIdx.x / t.nchunks, c = blockIdx.x % t.nchunks;
+  const int64_t J = (a.n_uniform + a.q - 1) / a.q;
+  double* rv = red + b * J * kNumRed;
+  double* out = t.gpart + (b * t.nchunks + c) * kPartOut;
+  voice_setup(a, b, S.vs, lane);
+  const double* v = S.vs.v;
+  const double* dv = S.vs.d;
   const double rc = a.rc;
+  if (c >= silent_chunk(v, rc)) {
+    for (int n = lane; n < kNumSums; n += kWave)
+      (n < kPartOut ? out[n] : rv[tail_index(n, c, J)]) = 0.0;
+    return;
+  }
+  // envelope values, then their adjoints, of the six ADSRs (the segment rows
+  // are not used here)
+  double (*env)[kWave] = reinterpret_cast<double (*)[kWave]>(&S.vs.seg);
+  static_assert(2 * kSegFields >= 6, "envelope rows");
+  const double* sums = t.sums + b * t.nchunks * 4;
+  const double lc[2] = {sums[c * 4], sums[c * 4 + 1]};
+  double Gend1 = 0.0, Gend2 = 0.0;
+  for (int64_t k = c + 1 + lane; k < t.nchunks; k += kWave) {
+    Gend1 += sums[k * 4 + 2];
+    Gend2 += sums[k * 4 + 3];
+  }
+  Gend1 = wave_sum(Gend1);
+  Gend2 = wave_sum(Gend2);
+
   const double kPitch = kLn2 / 12.0;
   const double note_off = v[1] * rc;
   const bool owned_lane = lane >= 1 && lane <= kSegsPerChunk;
   const int64_t j = c * kSegsPerChunk - 1 + lane;
   const double jd = (double)j;
-  const bool inr = j >= 0 && j < J;
+  const bool inr = j >= 0 && j < J && lane <= kSegsPerChunk;
   const bool own = owned_lane && inr;
-  double R[kNumRed];
-#pragma unroll
-  for (int r = 0; r < kNumRed; ++r) R[r] = inr ? rv[j * kNumRed + r] : 0.0;
-  // segment phase adjoints: later segments of this chunk + those of later chunks
-  const double D1 = own ? R[kRD1] : 0.0, D2 = own ? R[kRD2] : 0.0;
-  const double Ge1 = Gend1 + wave_rev_excl_scan(D1, lane);
-  const double Ge2 = Gend2 + wave_rev_excl_scan(D2, lane);
-  // lane 0 (segment 62c - 1) needs the sum over all of this chunk's segments.
-  // The shuffles run on every lane: a cross-lane read from a lane that is
-  // masked off by a branch returns no data.
-  const double ge1_1 = __shfl(Ge1, 1), d1_1 = __shfl(D1, 1);
-  const double ge2_1 = __shfl(Ge2, 1), d2_1 = __shfl(D2, 1);
-  const double G1 = lane == 0 ? ge1_1 + d1_1 : Ge1;
-  const double G2 = lane == 0 ? ge2_1 + d2_1 : Ge2;
-  const double B01 = (G1 + R[kRD1]) * R[kRC01] - R[kRE01];
-  const double B11 = (G1 + R[kRD1]) * R[kRC11] - R[kRE11];
-  const double B02 = (G2 + R[kRD2]) * R[kRC02] - R[kRE02];
-  const double B12 = (G2 + R[kRD2]) * R[kRC12] - R[kRE12];
-  // right-end contributions come from the previous segment (lane - 1)
-  const double pB11 = __shfl_up(B11, 1), pB12 = __shfl_up(B12, 1);
-  const double pA11 = __shfl_up(R[kRA11], 1), pA13 = __shfl_up(R[kRA13], 1);
-  const double pA14 = __shfl_up(R[kRA14], 1);
   const bool lastj = (j == J - 1);
 
   // forward recompute at control sample j
-  EnvEval E[6];
+#pragma unroll 1
+  for (int k = 0; k < 6; ++k) env[k][lane] = adsr_value(dv, k, jd, note_off);
+  double x[4] = {env[0][lane], env[1][lane], 0.0, 0.0};
+  double ph[2], lfo[2], fpre[2], sn[2], cs[2];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) E[k] = env_eval(dv, k, jd, note_off);
-  double ph[2], shp[2][5], lfo[2], fpre[2];
-  {
+  for (int i = 0; i < 2; ++i) {
     // LFO phase: carry at the chunk's first owned sample + exclusive scan
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int pb = 32 + 8 * i;
-      fpre[i] = v[pb] + v[pb + 1] * E[2 + 2 * i].env;
-      const double inc = owned_lane ? fmax(0.0, fpre[i]) / rc : 0.0;
-      double incl = inc;
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const double t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-      }
-      const double th = lc[i] + (incl - inc);
-      const double p = th - floor(th);
-      ph[i] = p;
-      shp[i][0] = (1.0 + sinpi(2.0 * p)) / 2.0;
-      shp[i][1] = 1.0 - fabs(2.0 * p - 1.0);
-      shp[i][2] = p;
-      shp[i][3] = 1.0 - p;
-      shp[i][4] = p < 0.5 ? 1.0 : 0.0;
-      const double num = v[pb + 3] * shp[i][0] + v[pb + 4] * shp[i][1] + v[pb + 5] * shp[i][2] +
-                         v[pb + 6] * shp[i][3] + v[pb + 7] * shp[i][4];
-      lfo[i] = num * dv[kLfoInvW + i];
-    }
+    const int pb = 32 + 8 * i;
+    fpre[i] = v[pb] + v[pb + 1] * env[2 + 2 * i][lane];
+    const double inc = owned_lane ? fmax(0.0, fpre[i]) / rc : 0.0;
+    const double th = lc[i] + wave_excl_scan(inc, lane);
+    const double p = th - floor(th);
+    ph[i] = p;
+    sincos_cycles_f64(p, sn[i], cs[i]);
+    const double num = v[pb + 3] * ((1.0 + sn[i]) / 2.0) + v[pb + 4] * (1.0 - fabs(2.0 * p - 1.0)) +
+                       v[pb + 5] * p + v[pb + 6] * (1.0 - p) + v[pb + 7] * (p < 0.5 ? 1.0 : 0.0);
+    lfo[i] = num * dv[kLfoInvW + i];
+    x[2 + i] = lfo[i] * env[3 + 2 * i][lane];
   }
-  const double x[4] = {E[0].env, E[1].env, lfo[0] * E[3].env, lfo[1] * E[5].env};
   double y[5];
 #pragma unroll
   for (int o = 0; o < 5; ++o) {
@@ -502,54 +581,65 @@ __device__ __forceinline__ void control_chunk(const RenderArgs& a, const VoiceSh
     y[o] = (v[pb] * x[0] + v[pb + 1] * x[1] + v[pb + 2] * x[2] + v[pb + 3] * x[3]) *
            dv[kMixInvNorm + o];
   }
-  double yn_p[2];
-  {
-    const double t0 = __shfl_down(y[0], 1), t2 = __shfl_down(y[2], 1);
-    yn_p[0] = lastj ? y[0] : t0;
-    yn_p[1] = lastj ? y[2] : t2;
-  }
 
-  // dy_o(j): transposed upsampling of the segment adjoints
+  // dy_o(j): transposed upsampling of the segment adjoints; the right-end
+  // contributions come from the previous segment (lane - 1).  The shuffles run
+  // on every lane: a cross-lane read from a lane that is masked off by a branch
+  // returns no data.
+  auto R = [&](int r) { return inr ? rv[r * J + j] : 0.0; };
   double dy[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if (own) {
-    const double b1 = B01 + (lane >= 1 ? pB11 : 0.0) + (lastj ? B11 : 0.0);
-    const double b2 = B02 + (lane >= 1 ? pB12 : 0.0) + (lastj ? B12 : 0.0);
-    dy[0] = v[69] * kPitch * b1;
-    dy[2] = v[72] * kPitch * b2;
-    dy[1] = R[kRA01] + pA11 + (lastj ? R[kRA11] : 0.0);
-    dy[3] = R[kRA03] + pA13 + (lastj ? R[kRA13] : 0.0);
-    dy[4] = R[kRA04] + pA14 + (lastj ? R[kRA14] : 0.0);
-    // pitch, phase, level, shape and K contributions of segment j
-    const double m1 = kPitch * (B01 + B11), m2 = kPitch * (B02 + B12);
-    gadd<GRADS>(gacc, 0, lane, m1 + m2);
-    gadd<GRADS>(gacc, 68, lane, m1);
-    gadd<GRADS>(gacc, 71, lane, m2);
-    gadd<GRADS>(gacc, 69, lane, kPitch * (y[0] * B01 + yn_p[0] * B11));
-    gadd<GRADS>(gacc, 72, lane, kPitch * (y[2] * B02 + yn_p[1] * B12));
-    gadd<GRADS>(gacc, 70, lane, R[kRD1] / kTwoPi);
-    gadd<GRADS>(gacc, 73, lane, R[kRD2] / kTwoPi);
-    gadd<GRADS>(gacc, 75, lane, R[kRL1]);
-    gadd<GRADS>(gacc, 76, lane, R[kRL2]);
-    gadd<GRADS>(gacc, 77, lane, R[kRL3]);
-    gadd<GRADS>(gacc, 74, lane, R[kRShape]);
-  }
-  // the square-saw gain K = 12000 / (f_hi log10 f_hi), f_hi from the highest pitch
-  const double dK = own ? R[kRK] : 0.0;
-  if (dK != 0.0) {
-    const double midi = v[0];
-    const double mh = midi + v[71] + fmax(0.0, v[72]);
-    const double m_hi = fmax(0.0, mh);
-    const double fh = 440.0 * exp2((m_hi - 69.0) / 12.0);
-    if (fh <= a.sr / 2.0) {
-      const double Kd = 12000.0 / (fh * log10(fh));
-      const double dKdf = -(Kd / fh) * (1.0 + 1.0 / log(fh));
-      const double dm = dK * dKdf * fh * kPitch;
-      if (mh >= 0.0) {
-        gadd<GRADS>(gacc, 0, lane, dm);
-        gadd<GRADS>(gacc, 71, lane, dm);
-        if (v[72] >= 0.0) gadd<GRADS>(gacc, 72, lane, dm);
+  {
+    double m[2], dep[2], phi[2];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const int o = 2 * w, rb = w ? kRD2 : kRD1;
+      const double Dl = R(rb), C0 = R(rb + 1), C1 = R(rb + 2), E0 = R(rb + 3), E1 = R(rb + 4);
+      const double D = own ? Dl : 0.0;
+      // segment phase adjoints: later segments of this chunk + those of later
+      // chunks; lane 0 (segment 62c - 1) needs all of this chunk's
+      const double Ge = (w ? Gend2 : Gend1) + wave_rev_excl_scan(D, lane);
+      const double B0 = (Ge + Dl) * C0 - E0;
+      const double B1 = (Ge + Dl) * C1 - E1;
+      const double pB1 = __shfl_up(B1, 1);
+      const double tn = __shfl_down(y[o], 1);
+      const double yn = lastj ? y[o] : tn;
+      const double bt = B0 + pB1 + (lastj ? B1 : 0.0);
+      dy[o] = own ? v[69 + 3 * w] * kPitch * bt : 0.0;
+      // pitch and phase contributions of segment j
+      m[w] = own ? kPitch * (B0 + B1) : 0.0;
+      dep[w] = own ? kPitch * (y[o] * B0 + yn * B1) : 0.0;
+      phi[w] = D / kTwoPi;
+    }
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      const int o = w == 0 ? 1 : w + 2, rb = kRA01 + 2 * w;
+      const double A0 = R(rb), A1 = R(rb + 1);
+      const double pA1 = __shfl_up(A1, 1);
+      dy[o] = own ? A0 + pA1 + (lastj ? A1 : 0.0) : 0.0;
+    }
+    double gmidi = m[0] + m[1], gtune = m[1], gdep = dep[1];
+    // the square-saw gain K = 12000 / (f_hi log10 f_hi), f_hi from the highest pitch
+    const double rK = R(kRK);
+    const double dK = own ? rK : 0.0;
+    if (dK != 0.0) {
+      const double mh = v[0] + v[71] + fmax(0.0, v[72]);
+      const double m_hi = fmax(0.0, mh);
+      const double fh = 440.0 * exp2((m_hi - 69.0) / 12.0);
+      if (fh <= a.sr / 2.0) {
+        const double Kd = 12000.0 / (fh * log10(fh));
+        const double dKdf = -(Kd / fh) * (1.0 + 1.0 / log(fh));
+        const double dm = dK * dKdf * fh * kPitch;
+        if (mh >= 0.0) {
+          gmidi += dm;
+          gtune += dm;
+          if (v[72] >= 0.0) gdep += dm;
+        }
       }
     }
+    const double rL1 = R(kRL1), rL2 = R(kRL2), rL3 = R(kRL3), rS = R(kRShape);
+    emit4(S.part, kRowOsc, lane, m[0], dep[0], phi[0], gtune);
+    emit4(S.part, kRowOsc + 4, lane, gdep, phi[1], own ? rS : 0.0, own ? rL1 : 0.0);
+    emit4(S.part, kRowOsc + 8, lane, own ? rL2 : 0.0, own ? rL3 : 0.0, gmidi, 0.0);
   }
 
   // modulation mixer: y_o = sum_i G_oi x_i / n_o, n_o = max(1, sum_i G_oi)
@@ -559,246 +649,156 @@ __device__ __forceinline__ void control_chunk(const RenderArgs& a, const VoiceSh
     const int pb = 48 + 4 * o;
     const double inv = dv[kMixInvNorm + o];
     const bool big = (v[pb] + v[pb + 1] + v[pb + 2] + v[pb + 3]) >= 1.0;
+    const double yo = big ? y[o] : 0.0, di = dy[o] * inv;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      dx[i] += v[pb + i] * dy[o] * inv;
-      if (own) gadd<GRADS>(gacc, pb + i, lane, dy[o] * (x[i] - (big ? y[o] : 0.0)) * inv);
-    }
+    for (int i = 0; i < 4; ++i) dx[i] += v[pb + i] * di;
+    // dy is 0 on the lanes that own no control sample
+    emit4(S.part, kRowMix + 4 * o, lane, di * (x[0] - yo), di * (x[1] - yo), di * (x[2] - yo),
+          di * (x[3] - yo));
   }
-  double denv[6] = {dx[0], dx[1], 0.0, 0.0, 0.0, 0.0};
   // LFOs
+  double tail[2];                        // d inc / d rate ADSR of a later phase adjoint
+  env[0][lane] = dx[0];
+  env[1][lane] = dx[1];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int pb = 32 + 8 * i;
-    const double dl = dx[2 + i] * E[3 + 2 * i].env;
-    denv[3 + 2 * i] += dx[2 + i] * lfo[i];
+    const double p = ph[i], erate = env[2 + 2 * i][lane];
+    const double dl = dx[2 + i] * env[3 + 2 * i][lane];
+    env[3 + 2 * i][lane] = dx[2 + i] * lfo[i];
     const double invW = dv[kLfoInvW + i];
-    double dph = 0.0;
+    double dph = 0.0, dw = 0.0;
     if (invW > 0.0) {
-      const double p = ph[i];
       const double sd = (p * 2.0 - 1.0) > 0.0 ? 1.0 : ((p * 2.0 - 1.0) < 0.0 ? -1.0 : 0.0);
-      const double der = v[pb + 3] * (0.5 * kTwoPi * cospi(2.0 * p)) + v[pb + 4] * (-2.0 * sd) +
-                         v[pb + 5] - v[pb + 6];
-      dph = own ? dl * der * invW : 0.0;
-      if (own)
-#pragma unroll
-        for (int k = 0; k < 5; ++k) gadd<GRADS>(gacc, pb + 3 + k, lane, dl * (shp[i][k] - lfo[i]) * invW);
+      const double der = v[pb + 3] * (0.5 * kTwoPi * cs[i]) + v[pb + 4] * (-2.0 * sd) + v[pb + 5] -
+                         v[pb + 6];
+      dw = own ? dl * invW : 0.0;
+      dph = dw * der;
     }
     // phase: d phi += dph / 2 pi; d inc(k) = sum_{j > k} dph(j)
-    if (own) gadd<GRADS>(gacc, pb + 2, lane, dph / kTwoPi);
-    const double later = Lsuf[i] + wave_rev_excl_scan(dph, lane);
-    {
-      double s = dph;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      dph_tot[i] = s;
-    }
-    if (own && fpre[i] >= 0.0) {
-      const double df = later / rc;
-      gadd<GRADS>(gacc, pb, lane, df);
-      gadd<GRADS>(gacc, pb + 1, lane, df * E[2 + 2 * i].env);
-      denv[2 + 2 * i] += df * v[pb + 1];
-    }
+    const bool live = own && fpre[i] >= 0.0;
+    const double unit = live ? 1.0 / rc : 0.0;
+    const double later = wave_rev_excl_scan(dph, lane);
+    const double df = live ? later / rc : 0.0;
+    env[2 + 2 * i][lane] = df * v[pb + 1];
+    tail[i] = unit * v[pb + 1];
+    const int sl = kRowLfo + 12 * i;
+    emit4(S.part, sl, lane, df, df * erate, dph / kTwoPi, dw * ((1.0 + sn[i]) / 2.0 - lfo[i]));
+    emit4(S.part, sl + 4, lane, dw * (1.0 - fabs(2.0 * p - 1.0) - lfo[i]), dw * (p - lfo[i]),
+          dw * (1.0 - p - lfo[i]), dw * ((p < 0.5 ? 1.0 : 0.0) - lfo[i]));
+    emit4(S.part, sl + 8, lane, unit, unit * erate, dph, 0.0);
   }
-  // ADSRs
-  if (own) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const int pb = 2 + 5 * k;
-      const EnvEval& e = E[k];
-      const double de = denv[k];
-      if (de == 0.0) continue;
+  // ADSRs: derivatives per unit of the envelope's adjoint (0 where neither it
+  // nor a later phase adjoint reaches the envelope)
+  double goff = 0.0;
+#pragma unroll 1
+  for (int k = 0; k < 6; ++k) {
+    const double de = own ? env[k][lane] : 0.0;
+    const double tl = k == 2 ? tail[0] : k == 4 ? tail[1] : 0.0;
+    double dA = 0.0, dD = 0.0, dS = 0.0, dR = 0.0, dO = 0.0, dal = 0.0;
+    if (de != 0.0 || tl != 0.0) {
       const double A = dv[kEnvA + k], D = dv[kEnvD + k], Rr = dv[kEnvR + k];
+      const double iA = dv[kEnvInvA + k], iD = dv[kEnvInvD + k], iR = dv[kEnvInvR + k];
       const double Sus = dv[kEnvS + k], al = dv[kEnvAlpha + k];
-      const double dPa = de * e.M * e.Pr;
-      const double dM = de * e.Pa * e.Pr;
-      const double dPr = de * e.Pa * e.M;
-      gadd<GRADS>(gacc, pb + 2, lane, dM * (1.0 - e.Pd));
+      double Pa, Pd, Pr, xa, xd, xr, la, ld, lr;
+      pow01_grad(ramp(jd, 0.0, A, iA), al, Pa, xa, la);
+      pow01_grad(1.0 - ramp(jd, A, D, iD), al, Pd, xd, ld);
+      pow01_grad(1.0 - ramp(jd, note_off, Rr, iR), al, Pr, xr, lr);
+      const double M = Sus + (1.0 - Sus) * Pd;
+      const double dPa = M * Pr, dM = Pa * Pr, dPr = Pa * M;
       const double dPd = dM * (1.0 - Sus);
-      double gx, ga, dA = 0.0, dD = 0.0, dR = 0.0, dO = 0.0, dal = 0.0;
-      pow01_grad(e.att, al, e.Pa, gx, ga);
-      dal += dPa * ga;
-      if (ramp_live(jd, 0.0, A, dv[kEnvInvA + k])) dA += dPa * gx * (-jd * dv[kEnvInvA + k] * dv[kEnvInvA + k]);
-      pow01_grad(1.0 - e.dec, al, e.Pd, gx, ga);
-      dal += dPd * ga;
-      if (ramp_live(jd, A, D, dv[kEnvInvD + k])) {
-        const double dd = -dPd * gx;       // d/d dec
-        dA += dd * (-dv[kEnvInvD + k]);
-        dD += dd * (-(jd - A) * dv[kEnvInvD + k] * dv[kEnvInvD + k]);
+      dS = dM * (1.0 - Pd);
+      dal = dPa * la + dPd * ld + dPr * lr;
+      if (ramp_live(jd, 0.0, A, iA)) dA += dPa * xa * (-jd * iA * iA);
+      if (ramp_live(jd, A, D, iD)) {
+        const double dd = -dPd * xd;       // d/d dec
+        dA += dd * (-iD);
+        dD += dd * (-(jd - A) * iD * iD);
       }
-      pow01_grad(1.0 - e.rel, al, e.Pr, gx, ga);
-      dal += dPr * ga;
-      if (ramp_live(jd, note_off, Rr, dv[kEnvInvR + k])) {
-        const double dr = -dPr * gx;       // d/d rel
-        dO += dr * (-dv[kEnvInvR + k]);
-        dR += dr * (-(jd - note_off) * dv[kEnvInvR + k] * dv[kEnvInvR + k]);
+      if (ramp_live(jd, note_off, Rr, iR)) {
+        const double dr = -dPr * xr;       // d/d rel
+        dO += dr * (-iR);
+        dR += dr * (-(jd - note_off) * iR * iR);
       }
-      gadd<GRADS>(gacc, pb + 0, lane, dA * rc);
-      gadd<GRADS>(gacc, pb + 1, lane, dD * rc);
-      gadd<GRADS>(gacc, pb + 3, lane, dR * rc);
-      gadd<GRADS>(gacc, pb + 4, lane, dal);
-      gadd<GRADS>(gacc, 1, lane, dO * rc);
+      dA *= rc;
+      dD *= rc;
+      dR *= rc;
+      dO *= rc;
     }
+    goff += de * dO;
+    emit4(S.part, kRowEnv + 8 * k, lane, de * dA, de * dD, de * dS, de * dR);
+    emit4(S.part, kRowEnv + 8 * k + 4, lane, de * dal, tl * dal, tl * dO, 0.0);
+    if (k == 2 || k == 4) emit4(S.part, kRowTail + 2 * k - 4, lane, tl * dA, tl * dD, tl * dS, tl * dR);
   }
-}
-
-// The control-rate adjoint runs chunk-parallel: one wavefront per (voice,
-// chunk).  The serial dependencies between chunks (LFO phases forward, the
-// phase-adjoint suffix sums backward) go through per-chunk totals stored by
-// earlier passes and combined in the order a single wavefront walking the
-// chunks would combine them, so every chunk sees the same inputs as in such
-// a walk.
-struct CtlArgs {
-  double* sums;      // [batch][chunks][4]: D1, D2 over owned segments; LFO 1, 2 increments
-  double* dph;       // [batch][chunks][2]: LFO 1, 2 phase-adjoint sums
-  double* gpart;     // [batch][chunks][78]: parameter adjoints per chunk (human values)
-  int64_t nchunks;
-};
-
-__device__ __forceinline__ double wave_sum(double x) {
+  emit4(S.part, kRowOff, lane, goff, 0.0, 0.0, 0.0);
+  __syncthreads();
+  for (int n = lane; n < kNumSums; n += kWave) {
+    const double* pr = S.part[sum_row(n)];
+    double s = 0.0;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-  return x;
-}
-
-// LFO phases at chunk c's first owned control sample and the phase-adjoint
-// sums of all later chunks, from the pass-0 totals (serial order).
-__device__ __forceinline__ void chunk_inputs(const VoiceShared& vs, const double* sums, int64_t c,
-                                             int64_t nchunks, double* lc, double& Gend1,
-                                             double& Gend2) {
-  lc[0] = vs.carry[0];
-  lc[1] = vs.carry[1];
-  for (int64_t k = 0; k < c; ++k) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      lc[i] += sums[k * 4 + 2 + i];
-      lc[i] -= floor(lc[i]);
-    }
-  }
-  Gend1 = 0.0;
-  Gend2 = 0.0;
-  for (int64_t k = nchunks - 1; k > c; --k) {
-    Gend1 += sums[k * 4];
-    Gend2 += sums[k * 4 + 1];
+    for (int l = 0; l < kWave / 16; ++l) s += pr[l];
+    (n < kPartOut ? out[n] : rv[tail_index(n, c, J)]) = s;
   }
 }
 
-// Pass 0: per chunk, D1 and D2 summed over its owned segments and both LFO
-// phase increments summed over its owned control samples.
-__global__ void __launch_bounds__(kWave) adjoint_chunk_sums_kernel(const RenderArgs a,
-                                                                   const double* __restrict__ red,
-                                                                   CtlArgs t) {
-  __shared__ VoiceShared vs;
-  const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x / t.nchunks, c = blockIdx.x % t.nchunks;
+// Per voice: the chunks' sums joined (last chunk first; the LFO factors times
+// the phase adjoints of the chunks after theirs) and taken through the curve
+// mapping's Jacobian to the normalised parameters.
+constexpr int kParamThreads = 128;
+__global__ void __launch_bounds__(kParamThreads) adjoint_params_kernel(const RenderArgs a,
+                                                                       const double* __restrict__ red,
+                                                                       CtlArgs t,
+                                                                       float* __restrict__ grad_params) {
+  __shared__ double tot[kNumSums];
+  const int p = threadIdx.x;
+  const int64_t b = blockIdx.x;
   const int64_t J = (a.n_uniform + a.q - 1) / a.q;
-  const double* rv = red + b * J * kNumRed;
-  voice_setup(a, b, vs, lane);
-  const double* v = vs.v;
-  const double* dv = vs.d;
-  const double rc = a.rc;
-  const double note_off = v[1] * rc;
-  const int64_t j = c * kSegsPerChunk - 1 + lane;
-  const bool owned_lane = lane >= 1 && lane <= kSegsPerChunk;
-  const bool own = owned_lane && j < J;            // owned lanes have j >= 0
-  const double s1 = wave_sum(own ? rv[j * kNumRed + kRD1] : 0.0);
-  const double s2 = wave_sum(own ? rv[j * kNumRed + kRD2] : 0.0);
-  double li[2];
+  if (p < kNumSums) {
+    const double* rv = red + b * J * kNumRed;
+    const double* gp = t.gpart + b * t.nchunks * kPartOut;
+    auto sum_of = [&](int n, int64_t c) {
+      return n < kPartOut ? gp[c * kPartOut + n] : rv[tail_index(n, c, J)];
+    };
+    double s = 0.0;
+    if (p < kSumTail || p >= kSumDph) {
+#pragma unroll 4
+      for (int64_t c = t.nchunks - 1; c >= 0; --c) s += sum_of(p, c);
+    } else {
+      const int dp = kSumDph + (p - kSumTail) / 8;
+      double later = 0.0;
+#pragma unroll 4
+      for (int64_t c = t.nchunks - 1; c >= 0; --c) {
+        const double f = sum_of(p, c), d = sum_of(dp, c);
+        if (later != 0.0) s += later * f;
+        later += d;
+      }
+    }
+    tot[p] = s;
+  }
+  __syncthreads();
+  if (p >= kNumParams) return;
+  double s = tot[p];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int pb = 32 + 8 * i;
-    const EnvEval Er = env_eval(dv, 2 + 2 * i, (double)j, note_off);
-    const double f = fmax(0.0, v[pb] + v[pb + 1] * Er.env);
-    li[i] = wave_sum(own ? f / rc : 0.0);
+    const int eb = 2 + 5 * (2 + 2 * i), lb = 32 + 8 * i, tb = kSumTail + 8 * i;
+    if (p >= eb && p < eb + 5) s += tot[tb + p - eb];
+    if (p == 1) s += tot[tb + 5];
+    if (p == lb || p == lb + 1) s += tot[tb + 6 + p - lb];
   }
-  if (lane == 0) {
-    double* o = t.sums + (b * t.nchunks + c) * 4;
-    o[0] = s1;
-    o[1] = s2;
-    o[2] = li[0];
-    o[3] = li[1];
+  const double u = (double)a.params[b * kNumParams + p];
+  const NebulaArgs& nb = a.neb;
+  const double span = nb.hi[p] - nb.lo[p];
+  const bool lin = bit(nb.linear, p);
+  const double e = nb.inv_curve[p];
+  double jac;
+  if (!bit(nb.sym, p)) {
+    jac = lin ? span : (u > 0.0 ? span * e * pow(u, e - 1.0) : 0.0);
+  } else {
+    const double d = 2.0 * u - 1.0;
+    const double ad = fabs(d);
+    jac = ad > 0.0 ? (lin ? span : span * e * pow(ad, e - 1.0)) : 0.0;
   }
-}
-
-// Pass 1: per chunk, the LFO phase-adjoint sums (they need the chunk's whole
-// forward recompute and mixer adjoint, not its parameter adjoints).
-__global__ void __launch_bounds__(kWave) adjoint_chunk_lfo_kernel(const RenderArgs a,
-                                                                  const double* __restrict__ red,
-                                                                  CtlArgs t) {
-  __shared__ VoiceShared vs;
-  const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x / t.nchunks, c = blockIdx.x % t.nchunks;
-  const int64_t J = (a.n_uniform + a.q - 1) / a.q;
-  voice_setup(a, b, vs, lane);
-  double lc[2], G1, G2;
-  chunk_inputs(vs, t.sums + b * t.nchunks * 4, c, t.nchunks, lc, G1, G2);
-  const double Lsuf[2] = {0.0, 0.0};
-  double tot[2];
-  control_chunk<false>(a, vs, nullptr, red + b * J * kNumRed, c, J, lane, G1, G2, lc, Lsuf, tot);
-  if (lane == 0) {
-    t.dph[(b * t.nchunks + c) * 2] = tot[0];
-    t.dph[(b * t.nchunks + c) * 2 + 1] = tot[1];
-  }
-}
-
-// Pass 2: per chunk, the parameter adjoints (human values), summed over the
-// lanes in lane order.
-struct GradShared {
-  VoiceShared vs;
-  double gacc[kNumParams][kAccRow];
-};
-
-__global__ void __launch_bounds__(kWave) adjoint_chunk_grad_kernel(const RenderArgs a,
-                                                                   const double* __restrict__ red,
-                                                                   CtlArgs t) {
-  __shared__ GradShared S;
-  const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x / t.nchunks, c = blockIdx.x % t.nchunks;
-  const int64_t J = (a.n_uniform + a.q - 1) / a.q;
-  for (int p = 0; p < kNumParams; ++p) S.gacc[p][lane] = 0.0;
-  voice_setup(a, b, S.vs, lane);
-  double lc[2], G1, G2;
-  chunk_inputs(S.vs, t.sums + b * t.nchunks * 4, c, t.nchunks, lc, G1, G2);
-  double Lsuf[2] = {0.0, 0.0};
-  for (int64_t k = t.nchunks - 1; k > c; --k) {
-    Lsuf[0] += t.dph[(b * t.nchunks + k) * 2];
-    Lsuf[1] += t.dph[(b * t.nchunks + k) * 2 + 1];
-  }
-  double tot[2];
-  control_chunk<true>(a, S.vs, S.gacc, red + b * J * kNumRed, c, J, lane, G1, G2, lc, Lsuf, tot);
-  __syncthreads();
-  for (int p = lane; p < kNumParams; p += kWave) {
-    double s = 0.0;
-    for (int l = 0; l < kWave; ++l) s += S.gacc[p][l];
-    t.gpart[(b * t.nchunks + c) * kNumParams + p] = s;
-  }
-}
-
-// Pass 3: per voice, the chunks' parameter adjoints summed (last chunk
-// first) and taken through the curve mapping's Jacobian to the normalised
-// parameters.
-__global__ void __launch_bounds__(kWave) adjoint_params_kernel(const RenderArgs a, CtlArgs t,
-                                                               float* __restrict__ grad_params) {
-  const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x;
-  for (int p = lane; p < kNumParams; p += kWave) {
-    double s = 0.0;
-    for (int64_t c = t.nchunks - 1; c >= 0; --c) s += t.gpart[(b * t.nchunks + c) * kNumParams + p];
-    const double u = (double)a.params[b * kNumParams + p];
-    const NebulaArgs& nb = a.neb;
-    const double span = nb.hi[p] - nb.lo[p];
-    const bool lin = bit(nb.linear, p);
-    const double e = nb.inv_curve[p];
-    double jac;
-    if (!bit(nb.sym, p)) {
-      jac = lin ? span : (u > 0.0 ? span * e * pow(u, e - 1.0) : 0.0);
-    } else {
-      const double d = 2.0 * u - 1.0;
-      const double ad = fabs(d);
-      jac = ad > 0.0 ? (lin ? span : span * e * pow(ad, e - 1.0)) : 0.0;
-    }
-    grad_params[b * kNumParams + p] = (float)(s * jac);
-  }
+  grad_params[b * kNumParams + p] = (float)(s * jac);
 }
 
 template <int RPS>
@@ -806,33 +806,31 @@ hipError_t launch_adjoint_rps(const RenderArgs& a, const float* g, double* red, 
                               hipStream_t s) {
   size_t shmem = (size_t)kWave * (a.q / RPS) * (sizeof(float) + sizeof(uint16_t));
   if (shmem < 8 * kWave * sizeof(double)) shmem = 8 * kWave * sizeof(double);
-  hipLaunchKernelGGL((adjoint_audio_kernel<RPS>), dim3((unsigned)(a.batch * a.slices)), dim3(kWave),
-                     shmem, s, a, g, red);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  // the control-rate passes' totals follow the segment sums and the carries
+  // the chunks' sums follow the segment sums
   const int64_t J = (a.n_uniform + a.q - 1) / a.q;
   CtlArgs t;
   t.nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
-  t.sums = red + a.batch * (J * kNumRed + t.nchunks * 4);
-  t.dph = t.sums + a.batch * t.nchunks * 4;
-  t.gpart = t.dph + a.batch * t.nchunks * 2;
-  const dim3 chunks((unsigned)(a.batch * t.nchunks));
-  hipLaunchKernelGGL(adjoint_chunk_sums_kernel, chunks, dim3(kWave), 0, s, a, red, t);
-  hipLaunchKernelGGL(adjoint_chunk_lfo_kernel, chunks, dim3(kWave), 0, s, a, red, t);
-  hipLaunchKernelGGL(adjoint_chunk_grad_kernel, chunks, dim3(kWave), 0, s, a, red, t);
-  hipLaunchKernelGGL(adjoint_params_kernel, dim3((unsigned)a.batch), dim3(kWave), 0, s, a, t, gp);
+  t.sums = adjoint_carries(red, a.batch, a.n_uniform, a.q);
+  t.gpart = t.sums + a.batch * t.nchunks * 4;
+  hipLaunchKernelGGL((adjoint_audio_kernel<RPS>), dim3((unsigned)(a.batch * a.slices)), dim3(kWave),
+                     shmem, s, a, g, red, t);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(adjoint_chunk_grad_kernel, dim3((unsigned)(a.batch * t.nchunks)), dim3(kWave), 0,
+                     s, a, red, t);
+  hipLaunchKernelGGL(adjoint_params_kernel, dim3((unsigned)a.batch), dim3(kParamThreads), 0, s, a, red,
+                     t, gp);
   return hipGetLastError();
 }
 
 }  // namespace
 
 size_t adjoint_workspace_bytes(int64_t batch, int64_t n_samples, int q) {
-  // per-segment sums [batch][J][21], the chunk-start carries [batch][chunks][4],
-  // then the control-rate passes' per-chunk totals [batch][chunks][4 + 2 + 78]
+  // per-segment sums [batch][21][J], the chunk-start carries (in their place
+  // later the chunks' sums) [batch][chunks][4], then the adjoint sums
   const int64_t J = (n_samples + q - 1) / q;
   const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
-  return (size_t)batch * ((size_t)J * kNumRed + (size_t)nchunks * (4 + 4 + 2 + kNumParams)) *
+  return (size_t)batch * ((size_t)J * kNumRed + (size_t)nchunks * (4 + kPartOut)) *
          sizeof(double);
 }
 
@@ -848,7 +846,6 @@ hipError_t launch_render_backward(const RenderArgs& a, const float* grad_audio, 
   if (a.batch == 0) return hipSuccess;
   switch (runs_per_segment) {
     case 1: return launch_adjoint_rps<1>(a, grad_audio, ws, grad_params, s);
-    case 2: return launch_adjoint_rps<2>(a, grad_audio, ws, grad_params, s);
     case 4: return launch_adjoint_rps<4>(a, grad_audio, ws, grad_params, s);
     default: return hipErrorInvalidValue;
   }
