@@ -6,8 +6,9 @@
 //   m_v = midi + tune_v + depth_v a_pitch_v
 //   y = L1 sin(2 pi theta_1) a_1 + L2 x2(theta_2) a_3 + L3 noise a_4
 //
-// Kernel A (one wavefront per voice) recomputes the forward with the render's
-// own control stage and phase recurrences and reduces, per control segment s,
+// Kernel A (one wavefront per chunk of a voice, or per slice of chunks)
+// recomputes the forward with the render's own control stage and phase
+// recurrences and reduces, per control segment s,
 //   D_v = sum dtheta_v,  C{0,1}_v = sum w{0,1} inc_v,  E{0,1}_v = sum w{0,1} inc_v P_v
 // (w0 = 1 - t, w1 = t, P_v the inclusive in-segment prefix of dtheta_v), the
 // VCA row sums A{0,1}_o = sum w{0,1} g L x, and the sums for the levels, the
@@ -18,12 +19,11 @@
 // (suffix) scan of the phase adjoint is split into an in-segment part (here)
 // and a cross-segment float64 scan (kernel B).
 //
-// Kernel B (one wavefront per voice) walks the control samples backward by
-// chunks: segment adjoints -> dy_o(j) (transposed upsampling), modulation
-// mixer, LFOs (shape weights, phase with its own suffix scan, rate clamp),
-// control-rate VCAs and the six ADSRs, accumulating d(human value) per lane in
-// LDS; then a fixed-order lane reduction and the curve-mapping Jacobian give
-// d/d(normalised parameter).  Deterministic; no atomics.
+// Kernel B (one wavefront per chunk): segment adjoints -> dy_o(j) (transposed
+// upsampling), modulation mixer, LFOs (shape weights, phase with its own suffix
+// scan, rate clamp), control-rate VCAs and the six ADSRs, d(human value) summed
+// over the chunk.  Kernel C joins a voice's chunks and applies the curve
+// mapping's Jacobian: d/d(normalised parameter).  Deterministic; no atomics.
 #include <math.h>
 
 #include <type_traits>
@@ -90,11 +90,10 @@ __device__ __forceinline__ double exp2_table(const double* tab, double y) {
   return ldexp(tab[n & 63] * p, n >> 6);
 }
 
-// Per chunk of a voice, after the segment sums red [batch][21][J]: its four
-// sums over the carries it started from (read by the audio workgroup that
-// starts there and by nobody after), and what the control-rate pass adds up.
+// What the control-rate pass reads and adds up per chunk of a voice, after the
+// segment sums red [batch][21][J].
 struct CtlArgs {
-  double* sums;      // [batch][chunks][4]: LFO 1, 2 phases at the chunk's start; D1, D2 over it
+  double* carries;   // [batch][chunks][4]: the phases at the chunk's start (LFO 1, 2 used)
   double* gpart;     // [batch][chunks][kPartOut]: adjoint sums of the chunk, the first kPartOut
   int64_t nchunks;
 };
@@ -125,12 +124,14 @@ __device__ __forceinline__ int64_t silent_chunk(const double* v, double rc) {
   return (js + kSegsPerChunk - 1) / kSegsPerChunk;
 }
 
-// Bound by float64 VALU issue at two wavefronts per SIMD: about 125
-// instructions a sample (205 with the series' sine and cosine, the weights,
-// ramps and products that follow from sums with and without the sample index
-// formed per sample, and the exponential's table in global memory); the render
-// adjoint of 256 voices of 4 s 710 -> 597 us.  LDS of 20.4 KB (noise as its 16-bit halves, 64 points
-// of the exponential) lets a CU hold the eight wavefronts the registers allow.
+// Bound by float64 VALU issue at two wavefronts per SIMD: 125 instructions a
+// sample, 92 of them float64 (205 with the series' sine and cosine, the
+// weights, ramps and products that follow from sums with and without the sample
+// index formed per sample, and the exponential's table in global memory); the
+// pass over 256 voices of 4 s 383 -> 298 us.  LDS of 20.4 KB (noise as its
+// 16-bit halves, 64 points of the exponential) lets a CU hold the eight
+// wavefronts the registers allow; fetching the next sample's table entries a
+// sample ahead changed nothing (301 us).
 template <int RPS>
 __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArgs a,
                                                               const float* __restrict__ g_audio,
@@ -139,8 +140,10 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
   __shared__ VoiceShared sh;
   extern __shared__ __align__(16) float tile[];
   const int lane = threadIdx.x;
-  const int64_t b = blockIdx.x / a.slices;
-  const int slice = (int)(blockIdx.x % a.slices);
+  const int per = a.slices * a.pass_split;       // workgroups per voice
+  const int64_t b = blockIdx.x / per;
+  const int part = (int)(blockIdx.x % per);
+  const int slice = part / a.pass_split, sub = part % a.pass_split;
   const int q = a.q;
   const int h = q / RPS;
   const double qd = (double)q;
@@ -149,7 +152,6 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
   const uint64_t g = a.voice_ids ? a.voice_ids[b] : a.first_g + (uint64_t)b;
   const float* gv = g_audio + b * N;
   double* rv = red + b * J * kNumRed;
-  double* cs = ctl.sums + b * ctl.nchunks * 4;
   float* tg = tile;                 // g(n) of the pass
   uint16_t* tn = reinterpret_cast<uint16_t*>(tile + kWave * h);   // 16-bit noise of the pass
   __shared__ double2 sct[256];
@@ -186,14 +188,10 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
     c_start = c_lo;
   }
   for (int64_t c = c_start; c < c_hi; ++c) {
-    if (c >= c_sil) {
-      // exactly silent from here on: no segment sums are read, only the chunks'
-      const int64_t s0 = c > c_lo ? c : c_lo;
-      for (int64_t i = lane; i < (c_hi - s0) * 4; i += kWave) cs[s0 * 4 + i] = 0.0;
-      break;
-    }
+    if (c >= c_sil) break;                       // no segment sums are read from there on
     double y[5], yn[5];
-    if (c >= c_lo && lane < 2) cs[c * 4 + lane] = sh.carry[lane];   // at the chunk's start
+    if (!a.carries && c >= c_lo && sub == 0 && lane < 2)
+      ctl.carries[(b * nchunks + c) * 4 + lane] = sh.carry[lane];
     __syncthreads();
     control_stage<RPS, false>(a, sh, reinterpret_cast<double*>(tile), c, J, h, lane, y, yn);
     if (c < c_lo) continue;                      // slice starts later: only carries needed
@@ -207,8 +205,7 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
     const int nseg = (int)((J - c * kSegsPerChunk) < kSegsPerChunk ? (J - c * kSegsPerChunk)
                                                                     : kSegsPerChunk);
     const int npass = (nseg + segs_pp - 1) / segs_pp;
-    double D1c = 0.0, D2c = 0.0;
-    for (int p = 0; p < npass; ++p) {
+    for (int p = sub; p < npass; p += a.pass_split) {
       // ---- load pass: g and the noise halves into LDS, 4 samples per lane ----
       const int64_t pbase = (c * kSegsPerChunk + (int64_t)p * segs_pp) * q;
       int64_t cnt64 = (int64_t)((nseg - p * segs_pp) < segs_pp ? (nseg - p * segs_pp) : segs_pp) * q;
@@ -385,16 +382,8 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
       if (m == 0 && ls < nseg) {
 #pragma unroll
         for (int r = 0; r < kNumRed; ++r) rv[r * J + sglob] = acc[r];
-        D1c += acc[kRD1];
-        D2c += acc[kRD2];
       }
       __syncthreads();
-    }
-    D1c = wave_sum(D1c);
-    D2c = wave_sum(D2c);
-    if (lane == 0) {
-      cs[c * 4 + 2] = D1c;
-      cs[c * 4 + 3] = D2c;
     }
   }
 }
@@ -500,15 +489,16 @@ __device__ __forceinline__ bool ramp_live(double jd, double s, double L, double 
 // control samples j = 62c .. 62c + 61 on lanes 1 .. 62 (lane l <-> j = 62c - 1
 // + l); lane 0 carries segment 62c - 1, whose right-end adjoint lands on lane
 // 1.  From the other chunks it needs the phase adjoints D of all later segments
-// and both LFO phases at control sample 62c, both left by the audio pass.
+// (summed here from their rows) and both LFO phases at control sample 62c.
 //
-// Bound by float64 issue (about 3000 instructions a chunk).  Two earlier
-// passes over the chunks (LFO phase totals, then the LFOs' phase adjoints) are
-// gone, the latter by the factors above, and the per-lane accumulators in LDS
-// (47.6 KB, three wavefronts per CU) by sums across lanes as the values come:
-// 256 voices of 4 s @TIME@.  The ADSRs are evaluated twice,
-// once for their values and once with their logarithms for the derivatives,
-// in loops over the six: kept in registers they cost the occupancy.
+// Bound by float64 issue: about 3100 instructions a chunk at three wavefronts
+// per SIMD.  Two earlier passes over the chunks (LFO phase totals, then the
+// LFOs' phase adjoints) are gone, the latter by the factors above, and the
+// per-lane accumulators in LDS (47.6 KB, three wavefronts per CU) by sums across
+// lanes as the values come: 256 voices of 4 s 285 us for three passes -> 75.
+// The ADSRs are evaluated twice, once for their values and once with their
+// logarithms for the derivatives, in loops over the six: kept in registers they
+// cost the occupancy.
 struct GradShared {
   VoiceShared vs;
   double part[kNumRows][kPartRow];
@@ -526,7 +516,8 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
   const double* v = S.vs.v;
   const double* dv = S.vs.d;
   const double rc = a.rc;
-  if (c >= silent_chunk(v, rc)) {
+  const int64_t c_sil = silent_chunk(v, rc);
+  if (c >= c_sil) {
     for (int n = lane; n < kNumSums; n += kWave)
       (n < kPartOut ? out[n] : rv[tail_index(n, c, J)]) = 0.0;
     return;
@@ -535,12 +526,13 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
   // are not used here)
   double (*env)[kWave] = reinterpret_cast<double (*)[kWave]>(&S.vs.seg);
   static_assert(2 * kSegFields >= 6, "envelope rows");
-  const double* sums = t.sums + b * t.nchunks * 4;
-  const double lc[2] = {sums[c * 4], sums[c * 4 + 1]};
+  const double* lc = t.carries + (b * t.nchunks + c) * 4;
   double Gend1 = 0.0, Gend2 = 0.0;
-  for (int64_t k = c + 1 + lane; k < t.nchunks; k += kWave) {
-    Gend1 += sums[k * 4 + 2];
-    Gend2 += sums[k * 4 + 3];
+  const int64_t Jl = c_sil < t.nchunks ? c_sil * kSegsPerChunk : J;   // later segments are 0
+#pragma unroll 4
+  for (int64_t k = (c + 1) * kSegsPerChunk + lane; k < Jl; k += kWave) {
+    Gend1 += rv[kRD1 * J + k];
+    Gend2 += rv[kRD2 * J + k];
   }
   Gend1 = wave_sum(Gend1);
   Gend2 = wave_sum(Gend2);
@@ -806,13 +798,13 @@ hipError_t launch_adjoint_rps(const RenderArgs& a, const float* g, double* red, 
                               hipStream_t s) {
   size_t shmem = (size_t)kWave * (a.q / RPS) * (sizeof(float) + sizeof(uint16_t));
   if (shmem < 8 * kWave * sizeof(double)) shmem = 8 * kWave * sizeof(double);
-  // the chunks' sums follow the segment sums
   const int64_t J = (a.n_uniform + a.q - 1) / a.q;
   CtlArgs t;
   t.nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
-  t.sums = adjoint_carries(red, a.batch, a.n_uniform, a.q);
-  t.gpart = t.sums + a.batch * t.nchunks * 4;
-  hipLaunchKernelGGL((adjoint_audio_kernel<RPS>), dim3((unsigned)(a.batch * a.slices)), dim3(kWave),
+  t.carries = adjoint_carries(red, a.batch, a.n_uniform, a.q);
+  t.gpart = t.carries + a.batch * t.nchunks * 4;
+  hipLaunchKernelGGL((adjoint_audio_kernel<RPS>), dim3((unsigned)(a.batch * a.slices * a.pass_split)),
+                     dim3(kWave),
                      shmem, s, a, g, red, t);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -826,8 +818,8 @@ hipError_t launch_adjoint_rps(const RenderArgs& a, const float* g, double* red, 
 }  // namespace
 
 size_t adjoint_workspace_bytes(int64_t batch, int64_t n_samples, int q) {
-  // per-segment sums [batch][21][J], the chunk-start carries (in their place
-  // later the chunks' sums) [batch][chunks][4], then the adjoint sums
+  // per-segment sums [batch][21][J], the chunk-start carries [batch][chunks][4],
+  // then the chunks' adjoint sums [batch][chunks][84]
   const int64_t J = (n_samples + q - 1) / q;
   const int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
   return (size_t)batch * ((size_t)J * kNumRed + (size_t)nchunks * (4 + kPartOut)) *
