@@ -14,11 +14,16 @@
 // last) into LDS, then every lane renders four
 // consecutive samples per step (lanes on consecutive 16-byte groups, so each
 // store instruction writes 1 KB of contiguous audio).  The four samples share
-// a control period; the phase n f_i / sr of the first is formed in float64
-// and reduced to [0, 1), the next three add f_i / sr in float32 (within
-// 2e-7 cycles), and the float32 hardware sine takes revolutions.  Periods
-// after every envelope has reached 0 are zero-filled without computation.
-// Bound by VALU issue: four sines and four modulated phases per sample.
+// a control period; the phase n f_i / sr of the first is a whole number of
+// 2^-64 cycles that wraps by itself and advances by one 64-bit addition per
+// step (n times the truncation of f_i / sr to that unit stays below 2^-38
+// cycles), its upper half the float32 phase in [0, 1]; the next three add
+// f_i / sr in float32 (within 2e-7 cycles), and the float32 hardware sine takes
+// revolutions.  Periods after every envelope has reached 0 are zero-filled
+// without computation.  Bound by VALU issue: four sines (quarter rate) and 25
+// other instructions per sample (33 with a float64 product, floor and
+// conversion per operator and step, and each envelope's two values read and
+// subtracted there): 16384 voices of 1 .. 4 s 2045 -> 1869 us.
 #include "voice_device.h"
 
 namespace synth {
@@ -56,7 +61,8 @@ struct FmArgs {
 __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
   __shared__ double v[kFmParams];
   __shared__ double dv[kDerived];
-  __shared__ float envs[4][65];
+  __shared__ __align__(16) float env0[64][4], envd[64][4];   // per period: value at its start, slope
+  __shared__ float last[4];                                 // value at the chunk's end
   const int lane = threadIdx.x;
   const int64_t b = a.order ? (int64_t)a.order[blockIdx.x] : (int64_t)blockIdx.x;
   if (b < 0 || b >= a.batch) return;         // an order entry out of range renders nothing
@@ -87,17 +93,21 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
   __syncthreads();
   const double note_off = v[1] * rc;
   // operator constants (uniform)
-  double inc[4];
+  uint64_t incx[4];                        // cycles per sample in units of 2^-64
   float lvl[4], incf[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int pb = kOpBase[i];
     const double f = 440.0 * voice::exp2_f64((v[0] - 69.0) / 12.0) * v[pb] *
                      voice::exp2_f64(v[pb + 1] / 1200.0);
-    inc[i] = fmin(f, a.sr / 2.0) / a.sr;
-    incf[i] = (float)inc[i];
+    const double inc = fmin(f, a.sr / 2.0) / a.sr;
+    incx[i] = (uint64_t)(inc * 0x1p64);
+    incf[i] = (float)inc;
     lvl[i] = (float)v[pb + 2];
   }
+  float nan0[4];                           // 0, or NaN for a NaN frequency
+#pragma unroll
+  for (int i = 0; i < 4; ++i) nan0[i] = 0.0f * incf[i];
   const float m01 = (float)v[kModBase], m02 = (float)v[kModBase + 1], m03 = (float)v[kModBase + 2];
   const float m12 = (float)v[kModBase + 3], m13 = (float)v[kModBase + 4];
   const float m23 = (float)v[kModBase + 5];
@@ -128,39 +138,46 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
       break;
     }
     // control values at j0 + 0 .. 64 (the last period holds its value): lane
-    // l evaluates j0 + l + 1; the value at j0 is the previous chunk's last
-    // one (the same control sample), so every lane works on each evaluation
+    // l evaluates j0 + l + 1, the end of period l, and takes its start from
+    // lane l - 1; the value at j0 is the previous chunk's last one (the same
+    // control sample).  Operator 0 modulates nothing: its mix weight is in its
+    // envelope.
     {
-      float carry[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) carry[i] = envs[i][64];
-      if (j0 == 0 && lane == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) carry[i] = lvl[i] * (float)adsr_value(dv, i, 0.0, note_off);
-      }
       const double jd = (double)min(j0 + lane + 1, J - 1);
+      float r[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) r[i] = lvl[i] * (float)adsr_value(dv, i, jd, note_off);
+      float l[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float e = lvl[i] * (float)adsr_value(dv, i, jd, note_off);
-        if (lane == 0) envs[i][0] = carry[i];
-        envs[i][lane + 1] = e;
+        l[i] = __shfl_up(r[i], 1);
+        if (lane == 0)
+          l[i] = j0 == 0 ? lvl[i] * (float)adsr_value(dv, i, 0.0, note_off) : last[i];
       }
+      *reinterpret_cast<float4*>(env0[lane]) = make_float4(w0 * l[0], l[1], l[2], l[3]);
+      *reinterpret_cast<float4*>(envd[lane]) =
+          make_float4(w0 * (r[0] - l[0]), r[1] - l[1], r[2] - l[2], r[3] - l[3]);
+      __syncthreads();                     // last is read before it is written
+      if (lane == 63) *reinterpret_cast<float4*>(last) = make_float4(r[0], r[1], r[2], r[3]);
     }
     __syncthreads();
+    uint64_t ph64[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ph64[i] = (uint64_t)(c0 + 4 * lane) * incx[i];
     for (int p = 4 * lane; p < cnt; p += 256) {
       // samples p .. p + 3 lie in one control period (q and p are multiples
-      // of 4): one period index, one float64 phase per operator, the other
-      // three phases and envelope values by float32 steps from it
+      // of 4): one period index, one phase per operator, the other three
+      // phases and envelope values by float32 steps from it
       const int seg = (int)__umulhi((uint32_t)p, a.q_magic);
       const float t0 = (float)(p - seg * a.q) * inv_q;
-      const double n0d = (double)(c0 + p);
-      float ph0[4], e0[4], de[4];
+      const float4 ev = *reinterpret_cast<const float4*>(env0[seg]);
+      const float4 dvv = *reinterpret_cast<const float4*>(envd[seg]);
+      const float e0[4] = {ev.x, ev.y, ev.z, ev.w}, de[4] = {dvv.x, dvv.y, dvv.z, dvv.w};
+      float ph0[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const double th = n0d * inc[i];
-        ph0[i] = (float)(th - floor(th));
-        e0[i] = envs[i][seg];
-        de[i] = envs[i][seg + 1] - e0[i];
+        ph0[i] = fmaf((float)(uint32_t)(ph64[i] >> 32), 0x1p-32f, nan0[i]);
+        ph64[i] += incx[i] << 8;
       }
       float y[4];
 #pragma unroll
@@ -175,9 +192,8 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
         const float o3 = en[3] * __builtin_amdgcn_sinf(ph[3]);
         const float o2 = en[2] * __builtin_amdgcn_sinf(fmaf(m23, o3, ph[2]));
         const float o1 = en[1] * __builtin_amdgcn_sinf(fmaf(m12, o2, fmaf(m13, o3, ph[1])));
-        const float o0 =
-            en[0] * __builtin_amdgcn_sinf(fmaf(m01, o1, fmaf(m02, o2, fmaf(m03, o3, ph[0]))));
-        y[e] = fmaf(w0, o0, fmaf(w1, o1, fmaf(w2, o2, w3 * o3)));
+        const float s0 = __builtin_amdgcn_sinf(fmaf(m01, o1, fmaf(m02, o2, fmaf(m03, o3, ph[0]))));
+        y[e] = fmaf(en[0], s0, fmaf(w1, o1, fmaf(w2, o2, w3 * o3)));
       }
       const int64_t n0 = c0 + p;
       if (vec && p + 4 <= cnt) {
