@@ -312,7 +312,9 @@ __device__ __forceinline__ double adsr_value(const double* dv, int k, double jd,
 // workgroup may take different chunks.  In two steps, because the VCO sums
 // need the LFO phases at the chunk's start: the first leaves the rate
 // envelopes and the rate scans of the chunk in the wavefront's scratch ws
-// (8 x 64 doubles).
+// (8 x 64 doubles).  Loops over two chains at a time: one at a time 12.2 us for
+// 8 voices of 1 s and 30.8 for 128 of 4 s, so 11.5 and 29.1 (powers without
+// branches, all chains overlapping: 13.0 and 37.9).
 enum { kCsEnv = 0, kCsLfo = 2, kCsScan = 4, kCsAmp = 6 };
 
 __device__ inline void lfo_chunk_sums(const RenderArgs& a, const double* v, const double* dv,
@@ -320,7 +322,7 @@ __device__ inline void lfo_chunk_sums(const RenderArgs& a, const double* v, cons
   const double rc = a.rc;
   const double note_off = v[1] * rc;
   const double jd = (double)(c * kSegsPerChunk + lane);
-#pragma unroll 1
+#pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int pb = 32 + 8 * i;
     const double f = fmax(0.0, v[pb] + v[pb + 1] * adsr_value(dv, 2 + 2 * i, jd, note_off));
@@ -344,12 +346,12 @@ __device__ inline void vco_chunk_sums(const RenderArgs& a, const double* v, cons
   const double midi = v[0];
   const int64_t j = c * kSegsPerChunk + lane;
   const double jd = (double)j;
-#pragma unroll 1
+#pragma unroll 2
   for (int k = 0; k < 4; ++k) {         // adsr_1, adsr_2 and the LFOs' amplitude ADSRs
     const double e = adsr_value(dv, k < 2 ? k : 2 * k - 1, jd, note_off);
     ws[(k < 2 ? kCsEnv + k : kCsAmp + k - 2) * kWave + lane] = e;
   }
-#pragma unroll 1
+#pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int pb = 32 + 8 * i;
     const double th = (i == 0 ? carry[0] : carry[1]) + ws[(kCsScan + i) * kWave + lane];
@@ -362,7 +364,7 @@ __device__ inline void vco_chunk_sums(const RenderArgs& a, const double* v, cons
   const double x0 = ws[lane], x1 = ws[kWave + lane];
   const double x2 = ws[2 * kWave + lane], x3 = ws[3 * kWave + lane];
   const bool last = (j + 1 >= J);
-#pragma unroll 1
+#pragma unroll
   for (int vc = 0; vc < 2; ++vc) {
     const int tb = vc ? 71 : 68;
     const int o = 2 * vc, pb = 48 + 4 * o;
