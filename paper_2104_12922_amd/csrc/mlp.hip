@@ -72,16 +72,30 @@ __global__ void __launch_bounds__(1024) colsum_kernel(const void* __restrict__ x
 // one 4-byte word, so a wavefront reads 256 contiguous bytes of a row;
 // wavefront w takes rows w, w + 4, ... of the slice), adds the four
 // wavefronts' sums in a fixed order and writes ws[r][col] (float64); the
-// second pass adds the slices in order.  Deterministic.
+// second pass adds the slices in order.  Deterministic.  Up to three matrices
+// of the same rows share the two launches, their column tiles one after the
+// other: a launch costs more than the sums (4096 rows of 1024 and 78 columns
+// 4 to 5 us each, twice per matrix; a training step of 4096 rows 389 -> 381 us).
 constexpr int kColTile = 128, kColWaves = 4;
 
-__global__ void __launch_bounds__(64 * kColWaves) colsum_part_kernel(const uint16_t* __restrict__ x,
-                                                                     int64_t rows, int64_t cols,
-                                                                     int64_t ld, int64_t r0n,
-                                                                     double* __restrict__ ws) {
+struct ColsumArgs {
+  const uint16_t* x[3];
+  float* sum[3];
+  int64_t cols[3], ld[3];
+  int tile0[4];              // first column tile of each matrix; the tiles in all
+  int64_t rows, r0n, slices;
+  double* ws;                // [slices][128 tiles]
+};
+
+__global__ void __launch_bounds__(64 * kColWaves) colsum_part_kernel(ColsumArgs a) {
   __shared__ double red[kColWaves][kColTile];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t c0 = blockIdx.x * (int64_t)kColTile + 2 * lane;
+  const int tile = (int)blockIdx.x, m = tile >= a.tile0[2] ? 2 : tile >= a.tile0[1] ? 1 : 0;
+  const uint16_t* __restrict__ x = m == 2 ? a.x[2] : m == 1 ? a.x[1] : a.x[0];
+  const int64_t cols = m == 2 ? a.cols[2] : m == 1 ? a.cols[1] : a.cols[0];
+  const int64_t ld = m == 2 ? a.ld[2] : m == 1 ? a.ld[1] : a.ld[0];
+  const int64_t rows = a.rows, r0n = a.r0n;
+  const int64_t c0 = (tile - (m == 2 ? a.tile0[2] : m == 1 ? a.tile0[1] : 0)) * (int64_t)kColTile + 2 * lane;
   const int64_t rb = blockIdx.y * r0n, re = min(rows, rb + r0n);
   double s0 = 0.0, s1 = 0.0;
   if (c0 + 1 < cols) {
@@ -113,27 +127,30 @@ __global__ void __launch_bounds__(64 * kColWaves) colsum_part_kernel(const uint1
     for (int e = 0; e < 2; ++e) {
       const int cc = 2 * lane + e;
       const double t = ((red[0][cc] + red[1][cc]) + red[2][cc]) + red[3][cc];
-      if (c0 + e < cols) ws[blockIdx.y * cols + c0 + e] = t;
+      if (c0 + e < cols)
+        a.ws[(blockIdx.y * (int64_t)a.tile0[3] + tile) * kColTile + cc] = t;
     }
   }
 }
 
-__global__ void __launch_bounds__(256) colsum_final_kernel(const double* __restrict__ ws,
-                                                           int64_t slices, int64_t cols,
-                                                           float* __restrict__ sum) {
-  const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (c >= cols) return;
+__global__ void __launch_bounds__(kColTile) colsum_final_kernel(ColsumArgs a) {
+  const int tile = (int)blockIdx.x, m = tile >= a.tile0[2] ? 2 : tile >= a.tile0[1] ? 1 : 0;
+  const int64_t c = (tile - (m == 2 ? a.tile0[2] : m == 1 ? a.tile0[1] : 0)) * (int64_t)kColTile +
+                    threadIdx.x;
+  if (c >= (m == 2 ? a.cols[2] : m == 1 ? a.cols[1] : a.cols[0])) return;
+  const double* ws = a.ws + tile * (int64_t)kColTile + threadIdx.x;
+  const int64_t row = (int64_t)a.tile0[3] * kColTile;
   double s = 0.0;
   int64_t r = 0;
-  for (; r + 8 <= slices; r += 8) {      // eight slices' loads in flight, added in order
+  for (; r + 8 <= a.slices; r += 8) {    // eight slices' loads in flight, added in order
     double v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = ws[(r + u) * cols + c];
+    for (int u = 0; u < 8; ++u) v[u] = ws[(r + u) * row];
 #pragma unroll
     for (int u = 0; u < 8; ++u) s += v[u];
   }
-  for (; r < slices; ++r) s += ws[r * cols + c];
-  sum[c] = (float)s;
+  for (; r < a.slices; ++r) s += ws[r * row];
+  (m == 2 ? a.sum[2] : m == 1 ? a.sum[1] : a.sum[0])[c] = (float)s;
 }
 
 // Per-column mean and 1 / sqrt(max(var, min_var)) (population variance), two
@@ -298,26 +315,47 @@ hipError_t launch_colsum(const void* x, int x_bf16, int64_t rows, int64_t cols, 
 
 size_t colsum_ws_bytes(int64_t rows, int64_t cols) {
   const int64_t slices = rows < 32 ? rows : 32;
-  return (size_t)(slices > 0 ? slices : 1) * (size_t)cols * sizeof(double);
+  const int64_t tiles = (cols + kColTile - 1) / kColTile;
+  return (size_t)(slices > 0 ? slices : 1) * (size_t)(tiles * kColTile) * sizeof(double);
 }
 
-hipError_t launch_colsum_bf16_ws(const void* x, int64_t rows, int64_t cols, int64_t ld, float* sum,
-                                 void* ws, size_t ws_bytes, hipStream_t s) {
-  if (cols == 0) return hipSuccess;
+hipError_t launch_colsums_bf16_ws(const ColsumMatrix* m, int n, int64_t rows, void* ws,
+                                  size_t ws_bytes, hipStream_t s) {
   // two-byte elements read in pairs: rows must start 4-byte aligned
-  const bool pairs = (ld % 2 == 0) && (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
-  if (!ws || ws_bytes < colsum_ws_bytes(rows, cols) || rows < 1 || !pairs ||
-      (reinterpret_cast<uintptr_t>(ws) & 7u) != 0)
-    return launch_colsum(x, 1, rows, cols, ld, sum, nullptr, s);
-  const int64_t slices = rows < 32 ? rows : 32;
-  const int64_t r0n = (rows + slices - 1) / slices;
-  const dim3 grid((unsigned)((cols + kColTile - 1) / kColTile), (unsigned)slices);
-  hipLaunchKernelGGL(colsum_part_kernel, grid, dim3(64 * kColWaves), 0, s,
-                     static_cast<const uint16_t*>(x), rows, cols, ld, r0n, static_cast<double*>(ws));
+  bool pairs = n >= 1 && n <= 3 && rows >= 1;
+  int64_t tiles = 0;
+  ColsumArgs a = {};
+  for (int i = 0; i < n && pairs; ++i) {
+    pairs = m[i].cols > 0 && m[i].ld % 2 == 0 && (reinterpret_cast<uintptr_t>(m[i].x) & 3u) == 0;
+    a.x[i] = static_cast<const uint16_t*>(m[i].x);
+    a.sum[i] = m[i].sum;
+    a.cols[i] = m[i].cols;
+    a.ld[i] = m[i].ld;
+    a.tile0[i] = (int)tiles;
+    tiles += (m[i].cols + kColTile - 1) / kColTile;
+    if (tiles > 0x7FFFFFFF) pairs = false;
+  }
+  for (int i = n; i < 4; ++i) a.tile0[i] = (int)tiles;
+  if (!ws || !pairs || ws_bytes < colsum_ws_bytes(rows, tiles * kColTile) ||
+      (reinterpret_cast<uintptr_t>(ws) & 7u) != 0) {
+    // one by one, where that fits the workspace or needs none
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = n > 1 ? launch_colsums_bf16_ws(m + i, 1, rows, ws, ws_bytes, s)
+                                 : launch_colsum(m[i].x, 1, rows, m[i].cols, m[i].ld, m[i].sum,
+                                                 nullptr, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  a.rows = rows;
+  a.slices = rows < 32 ? rows : 32;
+  a.r0n = (rows + a.slices - 1) / a.slices;
+  a.ws = static_cast<double*>(ws);
+  hipLaunchKernelGGL(colsum_part_kernel, dim3((unsigned)tiles, (unsigned)a.slices),
+                     dim3(64 * kColWaves), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, s,
-                     static_cast<const double*>(ws), slices, cols, sum);
+  hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)tiles), dim3(kColTile), 0, s, a);
   return hipGetLastError();
 }
 
