@@ -50,6 +50,7 @@ namespace synth {
 namespace {
 
 using voice::kLn2;
+using voice::dpp_f64;
 using voice::kTwoPi;
 using voice::sincos_cycles_f64;
 
@@ -278,32 +279,45 @@ __device__ __forceinline__ void stage_out(const float* lds, float* __restrict__ 
   }
 }
 
+// One step of the scan below: the lanes with `has` apply their map after the
+// one that `from` brings.
+template <class F>
+__device__ __forceinline__ void scan_step(Mat2& M, double& z0, double& z1, bool has, F&& from) {
+  const Mat2 P = {from(M.m00), from(M.m01), from(M.m10), from(M.m11)};
+  const double p0 = from(z0), p1 = from(z1);
+  if (has) {
+    const double n0 = fma(M.m00, p0, fma(M.m01, p1, z0));
+    const double n1 = fma(M.m10, p0, fma(M.m11, p1, z1));
+    M = mat_mul(M, P);
+    z0 = n0;
+    z1 = n1;
+  }
+}
+
 // Inclusive scan over lanes of the affine maps v -> M v + z, earlier lanes
-// applied first (dir = +1: lane - d is earlier; dir = -1: lane + d is).
+// applied first (DIR = +1: lower lanes are earlier; DIR = -1: higher ones).
+// By data-parallel moves within the rows of 16 and, upwards, across them (six
+// doubles a step; as shuffles through LDS they waited behind the sweeps' reads
+// of the CU's other wavefronts: forward and adjoint of 4096 voices 2184 -> 2133
+// us, the adjoint 1602 -> 1531).
 template <int DIR>
 __device__ __forceinline__ void scan_affine(Mat2& M, double& z0, double& z1) {
-  const int lane = threadIdx.x;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    Mat2 P;
-    double p0, p1;
-    if (DIR > 0) {
-      P.m00 = __shfl_up(M.m00, d); P.m01 = __shfl_up(M.m01, d);
-      P.m10 = __shfl_up(M.m10, d); P.m11 = __shfl_up(M.m11, d);
-      p0 = __shfl_up(z0, d); p1 = __shfl_up(z1, d);
-    } else {
-      P.m00 = __shfl_down(M.m00, d); P.m01 = __shfl_down(M.m01, d);
-      P.m10 = __shfl_down(M.m10, d); P.m11 = __shfl_down(M.m11, d);
-      p0 = __shfl_down(z0, d); p1 = __shfl_down(z1, d);
-    }
-    const bool has = DIR > 0 ? lane >= d : lane + d < 64;
-    if (has) {
-      const double n0 = fma(M.m00, p0, fma(M.m01, p1, z0));
-      const double n1 = fma(M.m10, p0, fma(M.m11, p1, z1));
-      M = mat_mul(M, P);
-      z0 = n0;
-      z1 = n1;
-    }
+  const int lane = threadIdx.x, l16 = lane & 15;
+  if constexpr (DIR > 0) {
+    scan_step(M, z0, z1, l16 >= 1, [](double x) { return dpp_f64<0x111>(x); });   // row_shr
+    scan_step(M, z0, z1, l16 >= 2, [](double x) { return dpp_f64<0x112>(x); });
+    scan_step(M, z0, z1, l16 >= 4, [](double x) { return dpp_f64<0x114>(x); });
+    scan_step(M, z0, z1, l16 >= 8, [](double x) { return dpp_f64<0x118>(x); });
+    scan_step(M, z0, z1, lane & 16, [](double x) { return dpp_f64<0x142, 0xa>(x); });   // row_bcast 15
+    scan_step(M, z0, z1, lane & 32, [](double x) { return dpp_f64<0x143, 0xc>(x); });   // row_bcast 31
+  } else {
+    scan_step(M, z0, z1, l16 + 1 < 16, [](double x) { return dpp_f64<0x101>(x); });     // row_shl
+    scan_step(M, z0, z1, l16 + 2 < 16, [](double x) { return dpp_f64<0x102>(x); });
+    scan_step(M, z0, z1, l16 + 4 < 16, [](double x) { return dpp_f64<0x104>(x); });
+    scan_step(M, z0, z1, l16 + 8 < 16, [](double x) { return dpp_f64<0x108>(x); });
+    const int next = (lane | 15) + 1;      // the next row's first lane
+    scan_step(M, z0, z1, !(lane & 16), [&](double x) { return __shfl(x, next & 63); });
+    scan_step(M, z0, z1, !(lane & 32), [](double x) { return __shfl(x, 32); });
   }
 }
 
