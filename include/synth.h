@@ -199,9 +199,8 @@ int synth_render_plan_ws(const synth_config* cfg, const float* params, const uin
 /* Workspace (bytes of device memory) that synth_render_backward needs for a
  * batch of uniform-length voices: batch * (ceil(n_samples / q) * 21 +
  * chunks * 88) doubles (per-segment sums; the chunk-start phase carries of
- * voices split over workgroups; per-chunk totals of the chunk-parallel
- * control-rate adjoint: 4 sums, 2 LFO phase adjoints, 78 parameter
- * adjoints; chunks = ceil(ceil(n_samples / q) / 62)).  Returns 0 for an
+ * voices split over workgroups; per-chunk sums of the chunk-parallel
+ * control-rate adjoint; chunks = ceil(ceil(n_samples / q) / 62)).  Returns 0 for an
  * invalid cfg. */
 size_t synth_render_backward_workspace(const synth_config* cfg, int64_t batch, int64_t n_samples);
 

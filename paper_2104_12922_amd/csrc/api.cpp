@@ -892,8 +892,9 @@ size_t synth_mlp_workspace(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_o
   if (batch <= 0 || d_in <= 0 || d_h <= 0 || d_out <= 0) return 0;
   int64_t sh[8][3];
   mlp_shapes(batch, d_in, d_h, d_out, sh);
-  // the bias gradients' column sums use it too (after the GEMMs)
-  size_t b = synth::colsum_ws_bytes(batch, d_h) * 2 + synth::colsum_ws_bytes(batch, d_out);
+  // the bias gradients' column sums use it too (after the GEMMs; one matrix
+  // after the other where it does not hold all three)
+  size_t b = synth::colsum_ws_bytes(batch, d_h > d_out ? d_h : d_out);
   for (auto& m : sh) {
     const size_t x = synth::gemm_split_bytes(m[0], m[1], synth::gemm_split_for(m[0], m[1], m[2]));
     b = x > b ? x : b;

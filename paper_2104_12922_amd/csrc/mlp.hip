@@ -82,9 +82,10 @@ struct ColsumArgs {
   const uint16_t* x[3];
   float* sum[3];
   int64_t cols[3], ld[3];
-  int tile0[4];              // first column tile of each matrix; the tiles in all
+  int64_t col0[4];           // columns before each matrix; the columns in all
+  int tile0[4];              // column tiles likewise
   int64_t rows, r0n, slices;
-  double* ws;                // [slices][128 tiles]
+  double* ws;                // [slices][col0[3]]
 };
 
 __global__ void __launch_bounds__(64 * kColWaves) colsum_part_kernel(ColsumArgs a) {
@@ -128,7 +129,7 @@ __global__ void __launch_bounds__(64 * kColWaves) colsum_part_kernel(ColsumArgs 
       const int cc = 2 * lane + e;
       const double t = ((red[0][cc] + red[1][cc]) + red[2][cc]) + red[3][cc];
       if (c0 + e < cols)
-        a.ws[(blockIdx.y * (int64_t)a.tile0[3] + tile) * kColTile + cc] = t;
+        a.ws[blockIdx.y * a.col0[3] + (m == 2 ? a.col0[2] : m == 1 ? a.col0[1] : 0) + c0 + e] = t;
     }
   }
 }
@@ -138,8 +139,8 @@ __global__ void __launch_bounds__(kColTile) colsum_final_kernel(ColsumArgs a) {
   const int64_t c = (tile - (m == 2 ? a.tile0[2] : m == 1 ? a.tile0[1] : 0)) * (int64_t)kColTile +
                     threadIdx.x;
   if (c >= (m == 2 ? a.cols[2] : m == 1 ? a.cols[1] : a.cols[0])) return;
-  const double* ws = a.ws + tile * (int64_t)kColTile + threadIdx.x;
-  const int64_t row = (int64_t)a.tile0[3] * kColTile;
+  const double* ws = a.ws + (m == 2 ? a.col0[2] : m == 1 ? a.col0[1] : 0) + c;
+  const int64_t row = a.col0[3];
   double s = 0.0;
   int64_t r = 0;
   for (; r + 8 <= a.slices; r += 8) {    // eight slices' loads in flight, added in order
@@ -315,15 +316,14 @@ hipError_t launch_colsum(const void* x, int x_bf16, int64_t rows, int64_t cols, 
 
 size_t colsum_ws_bytes(int64_t rows, int64_t cols) {
   const int64_t slices = rows < 32 ? rows : 32;
-  const int64_t tiles = (cols + kColTile - 1) / kColTile;
-  return (size_t)(slices > 0 ? slices : 1) * (size_t)(tiles * kColTile) * sizeof(double);
+  return (size_t)(slices > 0 ? slices : 1) * (size_t)cols * sizeof(double);
 }
 
 hipError_t launch_colsums_bf16_ws(const ColsumMatrix* m, int n, int64_t rows, void* ws,
                                   size_t ws_bytes, hipStream_t s) {
   // two-byte elements read in pairs: rows must start 4-byte aligned
   bool pairs = n >= 1 && n <= 3 && rows >= 1;
-  int64_t tiles = 0;
+  int64_t tiles = 0, cols = 0;
   ColsumArgs a = {};
   for (int i = 0; i < n && pairs; ++i) {
     pairs = m[i].cols > 0 && m[i].ld % 2 == 0 && (reinterpret_cast<uintptr_t>(m[i].x) & 3u) == 0;
@@ -331,12 +331,17 @@ hipError_t launch_colsums_bf16_ws(const ColsumMatrix* m, int n, int64_t rows, vo
     a.sum[i] = m[i].sum;
     a.cols[i] = m[i].cols;
     a.ld[i] = m[i].ld;
+    a.col0[i] = cols;
     a.tile0[i] = (int)tiles;
+    cols += m[i].cols;
     tiles += (m[i].cols + kColTile - 1) / kColTile;
     if (tiles > 0x7FFFFFFF) pairs = false;
   }
-  for (int i = n; i < 4; ++i) a.tile0[i] = (int)tiles;
-  if (!ws || !pairs || ws_bytes < colsum_ws_bytes(rows, tiles * kColTile) ||
+  for (int i = n; i < 4; ++i) {
+    a.col0[i] = cols;
+    a.tile0[i] = (int)tiles;
+  }
+  if (!ws || !pairs || ws_bytes < colsum_ws_bytes(rows, cols) ||
       (reinterpret_cast<uintptr_t>(ws) & 7u) != 0) {
     // one by one, where that fits the workspace or needs none
     for (int i = 0; i < n; ++i) {

@@ -125,9 +125,9 @@ hipError_t launch_vcf_backward(const float* x, const float* g, const int64_t* of
 hipError_t launch_colsum(const void* x, int x_bf16, int64_t rows, int64_t cols, int64_t ld,
                          float* sum, float* sumsq, hipStream_t s);
 // Column sums of up to three bf16 matrices of the same rows (bias gradients) in two deterministic passes
-// through a float64 workspace of colsum_ws_bytes(rows, cols) bytes added up (one
-// matrix after the other when it holds only one, and
-// launch_colsum for a matrix it cannot hold).
+// through a float64 workspace of colsum_ws_bytes(rows, cols) of all their columns (one
+// matrix after the other where it holds only one, launch_colsum for a matrix
+// it cannot hold).
 size_t colsum_ws_bytes(int64_t rows, int64_t cols);
 struct ColsumMatrix {
   const void* x;             // bf16 [rows][ld]
