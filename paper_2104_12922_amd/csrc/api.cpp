@@ -769,7 +769,7 @@ int synth_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, in
   if (n < 0 || m < 0 || dim < 0 || n > kMaxSet || m > kMaxSet || !out) return SYNTH_EINVAL;
   if (lda < dim || ldb < dim) return SYNTH_EINVAL;
   if (n > 0 && m > 0 && dim > 0 && (!A || !B)) return SYNTH_EINVAL;
-  const size_t need = synth_l1_pair_sum_workspace(n, m, dim);
+  const size_t need = n > 0 && m > 0 ? synth::l1_pair_sum_need(n, m, dim) : 0;
   if (need > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 7))) return SYNTH_EINVAL;
   if (workspace_bytes < need) return SYNTH_ENOMEM;
   return to_status(synth::launch_l1_pair_sum(A, lda, n, B, ldb, m, dim, (double*)workspace, out,
@@ -781,7 +781,7 @@ int synth_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t d
   if (n < 1 || m < 1 || dim < 0 || n > kMaxSet || m > kMaxSet || !out) return SYNTH_EINVAL;
   if (dim > 0 && (!X || !Y)) return SYNTH_EINVAL;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 7)) return SYNTH_EINVAL;
-  if (workspace_bytes < synth_mmd_l1_workspace(n, m, dim)) return SYNTH_ENOMEM;
+  if (workspace_bytes < synth::mmd_l1_need(n, m, dim)) return SYNTH_ENOMEM;
   return to_status(synth::launch_mmd_l1(X, n, Y, m, dim, (double*)workspace, out,
                                         (hipStream_t)stream));
 }

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(1024) colsum_kernel(const void* __restrict__ x
 // second pass adds the slices in order.  Deterministic.  Up to three matrices
 // of the same rows share the two launches, their column tiles one after the
 // other: a launch costs more than the sums (4096 rows of 1024 and 78 columns
-// 4 to 5 us each, twice per matrix; a training step of 4096 rows 389 -> 381 us).
+// 4 to 5 us each, twice per matrix; a training step of 4096 rows 389 -> 373 us).
 constexpr int kColTile = 128, kColWaves = 4;
 
 struct ColsumArgs {

@@ -21,6 +21,8 @@
 // order, so S is bitwise reproducible and S(X, X) equals S(A = X, B = X).
 // Bound by VALU issue: two instructions (subtract, add of the absolute
 // value) per pair and dimension.
+#include <algorithm>
+
 #include "synth_internal.h"
 
 namespace synth {
@@ -576,10 +578,17 @@ hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float*
 
 }  // namespace
 
-size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
+size_t l1_pair_sum_need(int64_t n, int64_t m, int64_t dim) {
   if (sort_one(n, m, dim)) return sort_bytes(n, m, dim);
   const PairPlan p = pair_plan(n, m, dim);
   return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+}
+
+// What a call needs or a sorted call of smaller sets would (up to 2048 sounds),
+// so that a workspace for the largest sets serves all.
+size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
+  return std::max(l1_pair_sum_need(n, m, dim),
+                  sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
 }
 
 hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
@@ -589,7 +598,7 @@ hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const floa
   return launch_all_pairs(A, lda, n, B, ldb, m, dim, partial, out, s);
 }
 
-size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
+size_t mmd_l1_need(int64_t n, int64_t m, int64_t dim) {
   if (sort_mmd(n, m, dim))
     return sort_bytes(n, m, dim);
   size_t need = 0;
@@ -598,6 +607,11 @@ size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
     need = b > need ? b : need;
   }
   return need;
+}
+
+size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
+  return std::max(mmd_l1_need(n, m, dim),
+                  sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
 }
 
 hipError_t launch_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,
