@@ -16,10 +16,10 @@
 // store instruction writes 1 KB of contiguous audio).  The four samples share
 // a control period; the phase n f_i / sr of the first is a whole number of
 // 2^-64 cycles that wraps by itself and advances by one 64-bit addition per
-// step (n times the truncation of f_i / sr to that unit stays below 2^-38
-// cycles), its upper half the float32 phase in [0, 1]; the next three add
-// f_i / sr in float32 (within 2e-7 cycles), and the float32 hardware sine takes
-// revolutions.  Periods after every envelope has reached 0 are zero-filled
+// step (n 2^-64 cycles from the truncation of f_i / sr to that unit, against
+// n f_i / sr 2^-53 from a float64 product), its upper half the float32 phase in
+// [0, 1] (2^-32 cycles); the next three add f_i / sr in float32 (within 2e-7
+// cycles), and the float32 hardware sine takes revolutions.  Periods after every envelope has reached 0 are zero-filled
 // without computation.  Bound by VALU issue: four sines (quarter rate) and 25
 // other instructions per sample (33 with a float64 product, floor and
 // conversion per operator and step, and each envelope's two values read and
@@ -100,12 +100,17 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
     const int pb = kOpBase[i];
     const double f = 440.0 * voice::exp2_f64((v[0] - 69.0) / 12.0) * v[pb] *
                      voice::exp2_f64(v[pb + 1] / 1200.0);
-    const double inc = fmin(f, a.sr / 2.0) / a.sr;
-    incx[i] = (uint64_t)(inc * 0x1p64);
+    // limited from above only: whole cycles below -1/2 are taken out (exactly),
+    // and a negative increment is the wrapped negative of its magnitude (a
+    // conversion of a negative number to unsigned is undefined)
+    double inc = fmin(f, a.sr / 2.0) / a.sr;
+    inc -= rint(inc);
+    const uint64_t mag = (uint64_t)(fabs(inc) * 0x1p64);
+    incx[i] = inc < 0.0 ? 0 - mag : mag;
     incf[i] = (float)inc;
     lvl[i] = (float)v[pb + 2];
   }
-  float nan0[4];                           // 0, or NaN for a NaN frequency
+  float nan0[4];                           // 0, or NaN for a frequency of minus infinity
 #pragma unroll
   for (int i = 0; i < 4; ++i) nan0[i] = 0.0f * incf[i];
   const float m01 = (float)v[kModBase], m02 = (float)v[kModBase + 1], m03 = (float)v[kModBase + 2];
