@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
   __shared__ double v[kFmParams];
   __shared__ double dv[kDerived];
   __shared__ __align__(16) float env0[64][4], envd[64][4];   // per period: value at its start, slope
-  __shared__ float last[4];                                 // value at the chunk's end
+  __shared__ __align__(16) float last[4];                    // value at the chunk's end
   const int lane = threadIdx.x;
   const int64_t b = a.order ? (int64_t)a.order[blockIdx.x] : (int64_t)blockIdx.x;
   if (b < 0 || b >= a.batch) return;         // an order entry out of range renders nothing
