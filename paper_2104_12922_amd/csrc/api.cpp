@@ -928,6 +928,13 @@ int synth_mlp_forward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, c
   return to_status(gemm_maybe_split(g, synth::kOpKMajor, synth::kOpKMajor, workspace, s));
 }
 
+namespace {
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const char *p = (const char*)a, *q = (const char*)b;
+  return p < q + b_bytes && q < p + a_bytes;
+}
+}  // namespace
+
 int synth_mlp_backward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, const void* x,
                        const void* w2t, const void* w3t, const float* h1pre, const void* h1,
                        const float* h2pre, const void* h2, const float* out, const float* target,
@@ -943,6 +950,21 @@ int synth_mlp_backward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, 
   hipStream_t s = (hipStream_t)stream;
   using synth::kOpKMajor;
   using synth::kOpRowMajorMN;
+  // The bias gradients are summed together after the last product, unless a
+  // caller laid a later result over scratch that no product reads by then (dh1
+  // or a weight gradient over dz3, dW1 over dh2): then each before that result.
+  const int64_t z3 = 2 * batch * d_out, z2 = 2 * batch * d_h;
+  const bool dz3_early = overlap(dz3, z3, dh1, z2) || overlap(dz3, z3, gw2t, 4 * d_h * d_h) ||
+                         overlap(dz3, z3, gw1t, 4 * d_h * d_in);
+  const bool dh2_early = overlap(dh2, z2, gw1t, 4 * d_h * d_in);
+  synth::ColsumMatrix late[3];
+  int n_late = 0;
+  auto column_sums = [&](const void* m, float* sum, int64_t cols, bool early) {
+    const synth::ColsumMatrix one = {m, sum, cols, cols};
+    if (early) return synth::launch_colsums_bf16_ws(&one, 1, batch, workspace, workspace_bytes, s);
+    late[n_late++] = one;
+    return hipSuccess;
+  };
   hipError_t e = synth::launch_mse_sigmoid_grad(out, target, batch, d_out, dz3, loss_rows, s);
   if (e != hipSuccess) return SYNTH_EDEVICE;
   synth::GemmArgs g = {};
@@ -951,6 +973,7 @@ int synth_mlp_backward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, 
   g.M = d_out; g.N = d_h; g.K = batch; g.A = dz3; g.lda = d_out; g.B = h2; g.ldb = d_h;
   g.C = gw3t; g.ldc = d_h; g.c_bf16 = 0;
   if ((e = gemm_maybe_split(g, kOpRowMajorMN, kOpRowMajorMN, workspace, s)) != hipSuccess) return SYNTH_EDEVICE;
+  if ((e = column_sums(dz3, gb3, d_out, dz3_early)) != hipSuccess) return SYNTH_EDEVICE;
   // dh2 = (dz3 W3^T^T) * gelu'(h2pre): A = dz3 [batch][d_out], B[k][n] = W3^T[k][n]
   g = {}; g.alpha = 1.0f;
   g.M = batch; g.N = d_h; g.K = d_out; g.A = dz3; g.lda = d_out; g.B = w3t; g.ldb = d_h;
@@ -961,6 +984,7 @@ int synth_mlp_backward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, 
   g.M = d_h; g.N = d_h; g.K = batch; g.A = dh2; g.lda = d_h; g.B = h1; g.ldb = d_h;
   g.C = gw2t; g.ldc = d_h;
   if ((e = gemm_maybe_split(g, kOpRowMajorMN, kOpRowMajorMN, workspace, s)) != hipSuccess) return SYNTH_EDEVICE;
+  if ((e = column_sums(dh2, gb2, d_h, dh2_early)) != hipSuccess) return SYNTH_EDEVICE;
   // dh1 = (dh2 W2^T^T) * gelu'(h1pre)
   g = {}; g.alpha = 1.0f;
   g.M = batch; g.N = d_h; g.K = d_h; g.A = dh2; g.lda = d_h; g.B = w2t; g.ldb = d_h;
@@ -971,9 +995,8 @@ int synth_mlp_backward(int64_t batch, int64_t d_in, int64_t d_h, int64_t d_out, 
   g.M = d_h; g.N = d_in; g.K = batch; g.A = dh1; g.lda = d_h; g.B = x; g.ldb = d_in;
   g.C = gw1t; g.ldc = d_in;
   if ((e = gemm_maybe_split(g, kOpRowMajorMN, kOpRowMajorMN, workspace, s)) != hipSuccess) return SYNTH_EDEVICE;
-  const synth::ColsumMatrix sums[3] = {
-      {dz3, gb3, d_out, d_out}, {dh2, gb2, d_h, d_h}, {dh1, gb1, d_h, d_h}};
-  return to_status(synth::launch_colsums_bf16_ws(sums, 3, batch, workspace, workspace_bytes, s));
+  column_sums(dh1, gb1, d_h, false);
+  return to_status(synth::launch_colsums_bf16_ws(late, n_late, batch, workspace, workspace_bytes, s));
 }
 
 int synth_logit_init(const float* u, float* z, float* u_out, int64_t n, float eps, void* stream) {
