@@ -446,11 +446,12 @@ int synth_scale_rows(const float* g, const double* s, int64_t rows, int64_t cols
  * reproducible.
  * ------------------------------------------------------------------------- */
 
-/* Bytes of device workspace synth_l1_pair_sum needs for sets of n and m
- * embeddings of dim floats (0 for an empty set or n, m above 2^17). */
+/* Bytes of device workspace that hold every synth_l1_pair_sum of sets of up to
+ * n and m embeddings of up to dim floats (0 for an empty set or n, m above
+ * 2^17): a workspace for the largest sets serves all. */
 size_t synth_l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim);
 
-/* Bytes of device workspace synth_mmd_l1 needs. */
+/* The same for synth_mmd_l1. */
 size_t synth_mmd_l1_workspace(int64_t n, int64_t m, int64_t dim);
 
 /* out[0] = S(A, B) (dev float64) for A dev float32 [n][dim] (row stride lda

@@ -561,6 +561,20 @@ size_t sort_bytes(int64_t n, int64_t m, int64_t dim) {
   return (size_t)((dim + c - 1) / c) * 3 * sizeof(double);
 }
 
+// Bytes that hold the partial sums of every call of at most these sizes, so that
+// a workspace for the largest sets serves all: it grows with each size, where
+// the need of a call does not (which way it goes depends on the sizes, and a
+// few tiles take more shares each).  All pairs of t tiles take t max(1, about
+// 1024 / t) partials: fewer than 2048 or one a tile, and at most one a run of
+// 256 dimensions and tile.
+size_t any_smaller_bytes(int64_t n, int64_t m, int64_t dim) {
+  const int64_t tiles = ((n + kPT - 1) / kPT) * ((m + kPT - 1) / kPT);
+  const int64_t runs = dim > 0 ? (dim + kF32Run - 1) / kF32Run : 1;
+  const int64_t pairs = std::min(tiles * runs, std::max(tiles, 2 * kFillBlocks));
+  return std::max((size_t)pairs * sizeof(double),
+                  sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
+}
+
 hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                             int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
   const PairPlan p = pair_plan(n, m, dim);
@@ -584,12 +598,7 @@ size_t l1_pair_sum_need(int64_t n, int64_t m, int64_t dim) {
   return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
 }
 
-// What a call needs or a sorted call of smaller sets would (up to 2048 sounds),
-// so that a workspace for the largest sets serves all.
-size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) {
-  return std::max(l1_pair_sum_need(n, m, dim),
-                  sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
-}
+size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) { return any_smaller_bytes(n, m, dim); }
 
 hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                               int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
@@ -610,8 +619,8 @@ size_t mmd_l1_need(int64_t n, int64_t m, int64_t dim) {
 }
 
 size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
-  return std::max(mmd_l1_need(n, m, dim),
-                  sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
+  const int64_t top = std::max(n, m);
+  return any_smaller_bytes(top, top, dim);
 }
 
 hipError_t launch_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,

@@ -104,7 +104,7 @@ hipError_t launch_sum_f64(const double* x, int64_t n, double scale, double* out,
 hipError_t launch_scale_rows(const float* g, const double* sc, int64_t rows, int64_t cols,
                              float* out, hipStream_t s);
 size_t l1_pair_sum_need(int64_t n, int64_t m, int64_t dim);        // bytes a call needs
-size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim);   // ... or one of smaller sets
+size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim);   // ... or any of smaller sizes
 hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                               int64_t m, int64_t dim, double* partial, double* out, hipStream_t s);
 size_t mmd_l1_need(int64_t n, int64_t m, int64_t dim);
