@@ -8,15 +8,17 @@
 
 #include <hip/hip_runtime.h>
 
+#include "render_plan.h"
 #include "synth.h"
 #include "synth_internal.h"
 
+using synth::chunks_of;
 using synth::NebulaArgs;
 using synth::RenderArgs;
 
 namespace {
 
-constexpr int kSegsPerChunk = 62;   // must match render.hip
+constexpr int kSegsPerChunk = synth::kChunkSegments;
 
 int to_status(hipError_t e) { return e == hipSuccess ? SYNTH_OK : SYNTH_EDEVICE; }
 
@@ -251,11 +253,6 @@ int synth_fm_render(const synth_fm_config* cfg, const float* params, int64_t bat
 }
 
 namespace {
-int64_t chunks_of(int64_t n_samples, int q) {
-  const int64_t J = (n_samples + q - 1) / q;
-  return (J + kSegsPerChunk - 1) / kSegsPerChunk;
-}
-
 int render_plan_impl(const synth_config* cfg, const float* params, const uint64_t* voice_ids,
                      uint64_t first_g, int64_t batch, const int64_t* offsets, int64_t n_samples,
                      int64_t max_samples, float* audio, int runs_per_segment,
@@ -350,52 +347,24 @@ int synth_render_plan_ws(const synth_config* cfg, const float* params, const uin
 }
 
 namespace {
-// The library's default plan: runs per segment 4 (1 if q is not a multiple
-// of 4); small uniform batches split each voice over workgroups so that the
-// grid covers the chip - at most a quarter of its chunks when the slices
-// walk the earlier chunks for their carries, up to all of them when the
-// carries are computed first, and then as many again, per chunk, as there are
-// passes (4) while the chip has fewer than two workgroups per CU (each forms
-// the chunk's control stage for itself, so only where no carries are walked).
-// With carries the aim is 8192 workgroups as soon as a voice is split (256
-// voices of 4 s: 139 us with 2048, 129 with 8192; 512: 303 and 270); the
-// passes halve the render of 8 voices of 1 s (25 -> 16 us).
-void default_plan(const synth_config* cfg, int64_t batch, const int64_t* offsets,
-                  int64_t n_samples, bool carried, int* rps, int* slices,
-                  int* pass_split = nullptr) {
-  *slices = 1;
-  *rps = 4;
-  if (pass_split) *pass_split = 1;
-  if (!cfg || !(cfg->control_rate > 0.0)) return;
-  const double q = nearbyint(cfg->sample_rate / cfg->control_rate);
-  if (fmod(q, 4.0) != 0.0) *rps = 1;
-  if (!offsets && n_samples > 0 && batch > 0 && q >= 4.0) {
-    const int64_t nchunks = chunks_of(n_samples, (int)q);
-    int64_t want = (2048 + batch - 1) / batch;
-    if (carried && want > 1) want = (8192 + batch - 1) / batch;
-    const int64_t cap = carried ? nchunks : nchunks / 4;
-    if (want > cap) want = cap;
-    if (want > 1) *slices = (int)want;
-    if (pass_split && *rps == 4 && (carried ? want > 1 : nchunks == 1)) {
-      while (*pass_split < 4 && batch * want * *pass_split < 512) *pass_split *= 2;
-    }
-  }
+synth::RenderPlan default_plan(const synth_config* cfg, int64_t batch, const int64_t* offsets,
+                               int64_t n_samples, bool carried) {
+  if (!cfg) return {4, 1, 1};
+  return synth::default_render_plan(cfg->sample_rate, cfg->control_rate, batch,
+                                    offsets ? 0 : n_samples, carried);
 }
 }  // namespace
 
 int synth_render(const synth_config* cfg, const float* params, const uint64_t* voice_ids,
                  uint64_t first_g, int64_t batch, const int64_t* offsets, int64_t n_samples,
                  float* audio, void* stream) {
-  int rps, slices, pass_split;
-  default_plan(cfg, batch, offsets, n_samples, false, &rps, &slices, &pass_split);
-  return render_plan_impl(cfg, params, voice_ids, first_g, batch, offsets, n_samples, 0, audio, rps,
-                          slices, 0, 0, nullptr, nullptr, 0, stream, pass_split);
+  const synth::RenderPlan p = default_plan(cfg, batch, offsets, n_samples, false);
+  return render_plan_impl(cfg, params, voice_ids, first_g, batch, offsets, n_samples, 0, audio,
+                          p.rps, p.slices, 0, 0, nullptr, nullptr, 0, stream, p.pass_split);
 }
 
 size_t synth_render_workspace(const synth_config* cfg, int64_t batch, int64_t n_samples) {
-  int rps, slices;
-  default_plan(cfg, batch, nullptr, n_samples, true, &rps, &slices);
-  if (slices <= 1 || batch > 65535) return 0;
+  if (default_plan(cfg, batch, nullptr, n_samples, true).slices <= 1 || batch > 65535) return 0;
   return synth_render_plan_workspace(cfg, batch, n_samples);
 }
 
@@ -405,11 +374,10 @@ int synth_render_ws(const synth_config* cfg, const float* params, const uint64_t
   if (!workspace || offsets) {
     return synth_render(cfg, params, voice_ids, first_g, batch, offsets, n_samples, audio, stream);
   }
-  int rps, slices, pass_split;
-  default_plan(cfg, batch, offsets, n_samples, true, &rps, &slices, &pass_split);
+  const synth::RenderPlan p = default_plan(cfg, batch, offsets, n_samples, true);
   return render_plan_impl(cfg, params, voice_ids, first_g, batch, offsets, n_samples, n_samples,
-                          audio, rps, slices, 0, 0, nullptr, workspace, workspace_bytes, stream,
-                          pass_split);
+                          audio, p.rps, p.slices, 0, 0, nullptr, workspace, workspace_bytes, stream,
+                          p.pass_split);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,57 @@
+// The library's default launch plan of a render (host arithmetic only).
+#pragma once
+
+#include <math.h>
+#include <stdint.h>
+
+namespace synth {
+
+constexpr int kChunkSegments = 62;   // control periods per chunk
+
+inline int64_t chunks_of(int64_t n_samples, int q) {
+  const int64_t J = (n_samples + q - 1) / q;
+  return (J + kChunkSegments - 1) / kChunkSegments;
+}
+
+struct RenderPlan {
+  int rps;          // runs per segment
+  int slices;       // parts of a voice's chunks, workgroups of their own
+  int pass_split;   // workgroups that share a slice's passes
+};
+
+// Runs per segment 4 (1 if q is not a multiple of 4); small uniform batches
+// (n_samples > 0) split each voice over workgroups so that the grid covers the
+// chip - at most a quarter of its chunks when the slices walk the earlier
+// chunks for their carries, up to all of them when the carries are computed
+// first (carried).
+//
+// Then the passes (of 16 control periods) of a chunk, up to 4, are split while
+// the chip has fewer than two workgroups per CU: each part forms the chunk's
+// control stage for itself, so only where no carries are walked, and a part
+// without a pass would be idle.  The passes halve the render of 8 voices of 1 s
+// (25 -> 16 us).
+//
+// With carries the aim is 8192 workgroups as soon as a voice is split (256
+// voices of 4 s: 139 us with 2048, 129 with 8192; 512: 303 and 270).
+inline RenderPlan default_render_plan(double sample_rate, double control_rate, int64_t batch,
+                                      int64_t n_samples, bool carried) {
+  RenderPlan p = {4, 1, 1};
+  if (!(control_rate > 0.0)) return p;
+  const double q = nearbyint(sample_rate / control_rate);
+  if (fmod(q, 4.0) != 0.0) p.rps = 1;
+  if (!(n_samples > 0 && batch > 0 && q >= 4.0)) return p;
+  const int64_t nchunks = chunks_of(n_samples, (int)q);
+  int64_t want = (2048 + batch - 1) / batch;
+  if (carried && want > 1) want = (8192 + batch - 1) / batch;
+  const int64_t cap = carried ? nchunks : nchunks / 4;
+  if (want > cap) want = cap;
+  if (want > 1) p.slices = (int)want;
+  if (p.rps == 4 && (carried ? p.slices > 1 : nchunks == 1)) {
+    const int64_t passes = ((n_samples + (int)q - 1) / (int)q + 15) / 16;
+    while (p.pass_split < 4 && p.pass_split < passes && batch * p.slices * p.pass_split < 512)
+      p.pass_split *= 2;
+  }
+  return p;
+}
+
+}  // namespace synth

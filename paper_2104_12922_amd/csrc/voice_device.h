@@ -5,6 +5,7 @@
 
 #include <math.h>
 
+#include "render_plan.h"
 #include "series_tables.h"
 #include "synth_internal.h"
 
@@ -12,7 +13,7 @@ namespace synth {
 namespace voice {
 
 constexpr int kWave = 64;
-constexpr int kSegsPerChunk = 62;
+constexpr int kSegsPerChunk = kChunkSegments;
 constexpr int kPointsPerChunk = kSegsPerChunk + 1;
 constexpr double kTwoPi = 6.283185307179586476925286766559;
 constexpr double kLn2 = 0.693147180559945309417232121458;
