@@ -358,6 +358,140 @@ __global__ void __launch_bounds__(kWave* kCarryWaves) voice_carries_kernel(const
   }
 }
 
+// The carries of a few long voices.  voice_carries_kernel takes 8 to 14 us for
+// every 16 chunks of a voice, one after the other (one voice of 60 s: 269 us
+// with its render), so from the third time on up to kLongVoices voices have a
+// workgroup for every 16 chunks, in three launches: the raw LFO sums of all
+// chunks, the raw VCO sums (each workgroup applies the LFO sums before its
+// chunks for itself), and the updates, one wavefront per voice.  The same
+// float64 operations in the same order.  Bound by the latency of the chains.
+// Renders in one launch and in three, us: 1 x 6 s 47 and 41, 1 x 60 s 269 and
+// 59, 16 x 30 s 171 and 69, 64 x 10 s 105 and 86, 128 x 10 s 188 and 180; with
+// more voices the one launch fills the chip (256 x 6 s 238 and 252, 512 x 8 s
+// 475 and 493), and with 32 chunks or fewer it is as fast (1 x 4 s 39 and 39).
+constexpr int kLongChunks = 32, kLongVoices = 128;
+constexpr int kCarryBlock = 256;     // chunks whose sums are staged in LDS at a time
+
+// carry' = (carry + t) - floor(carry + t) over the n values t[0], t[step], ...
+__device__ __forceinline__ double advance_carry(double carry, const double* t, int step, int n) {
+#pragma unroll 4
+  for (int i = 0; i < n; ++i) {
+    const double nc = carry + t[i * step];
+    carry = nc - floor(nc);
+  }
+  return carry;
+}
+
+// STEP 0: LFO sums into carries[..][0..1]; 1: VCO sums into carries[..][2..3].
+// Grid: (16 chunks, voice).
+template <int RPS, bool CLAMP, int STEP>
+__global__ void __launch_bounds__(kWave* kCarryWaves) long_carry_sums_kernel(const RenderArgs a,
+                                                                            double* carries,
+                                                                            int64_t stride) {
+  __shared__ VoiceShared sh;
+  __shared__ double scratch[kCarryWaves][8 * kWave];
+  __shared__ double2 lfo[kCarryBlock];           // raw sums, then the phases at this group's chunks
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t b = blockIdx.y, base = blockIdx.x * (int64_t)kCarryWaves, c = base + wave;
+  int64_t off0 = 0, N = a.n_uniform;
+  if (a.offsets) packed_range(a.offsets, a.batch, b, off0, N);
+  if (N <= 0) return;
+  const int64_t J = (N + a.q - 1) / a.q;
+  int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
+  if (nchunks > stride) nchunks = stride;
+  if (base >= nchunks) return;
+  double* cr = carries + b * stride * 4;
+  voice_setup(a, b, sh, threadIdx.x);
+  double t[2] = {0.0, 0.0};
+  if (c < nchunks) lfo_chunk_sums(a, sh.v, sh.d, scratch[wave], c, lane, t);
+  if constexpr (STEP == 0) {
+    if (c < nchunks && lane == 0) {
+      cr[4 * c] = t[0];
+      cr[4 * c + 1] = t[1];
+    }
+  } else {
+    // the LFO phases at the group's chunks: all sums before them, lanes 0 and 1
+    // of the first wavefront
+    double mine = sh.carry[lane & 1];
+    for (int64_t s0 = 0; s0 < base; s0 += kCarryBlock) {
+      const int n = (int)(base - s0 < kCarryBlock ? base - s0 : kCarryBlock);
+      __syncthreads();
+      if ((int)threadIdx.x < n) {
+        const double* p = cr + 4 * (s0 + threadIdx.x);
+        lfo[threadIdx.x] = make_double2(p[0], p[1]);
+      }
+      __syncthreads();
+      if (wave == 0 && lane < 2) mine = advance_carry(mine, &lfo[0].x + lane, 2, n);
+    }
+    __syncthreads();
+    if (lane == 0) lfo[wave] = make_double2(t[0], t[1]);
+    __syncthreads();
+    if (wave == 0 && lane < 2) {
+      double* l = &lfo[0].x + lane;
+      for (int i = 0; i < kCarryWaves; ++i) {
+        const double raw = l[2 * i];
+        l[2 * i] = mine;
+        mine = advance_carry(mine, &raw, 1, 1);
+      }
+    }
+    __syncthreads();
+    if (c < nchunks) {
+      const double carry[2] = {lfo[wave].x, lfo[wave].y};
+      vco_chunk_sums<RPS, CLAMP>(a, sh.v, sh.d, scratch[wave], c, J, a.q / RPS, lane, carry, t);
+      if (lane == 0) {
+        cr[4 * c + 2] = t[0];
+        cr[4 * c + 3] = t[1];
+      }
+    }
+  }
+}
+
+// The four sums of every chunk, in place, to the phases at its start.
+__global__ void __launch_bounds__(kWave) long_carry_scan_kernel(const RenderArgs a, double* carries,
+                                                                int64_t stride) {
+  __shared__ VoiceShared sh;
+  __shared__ double t[kWave][4];
+  const int lane = threadIdx.x;
+  const int64_t b = blockIdx.x;
+  int64_t off0 = 0, N = a.n_uniform;
+  if (a.offsets) packed_range(a.offsets, a.batch, b, off0, N);
+  if (N <= 0) return;
+  const int64_t J = (N + a.q - 1) / a.q;
+  int64_t nchunks = (J + kSegsPerChunk - 1) / kSegsPerChunk;
+  if (nchunks > stride) nchunks = stride;
+  double* cr = carries + b * stride * 4;
+  voice_setup(a, b, sh, lane);
+  double carry = sh.carry[lane & 3];
+  double next[4] = {0.0, 0.0, 0.0, 0.0};
+  auto fetch = [&](int64_t c) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) next[k] = c < nchunks ? cr[4 * c + k] : 0.0;
+  };
+  fetch(lane);
+  for (int64_t base = 0; base < nchunks; base += kWave) {
+    const int64_t c = base + lane;
+    const int n = (int)(nchunks - base < kWave ? nchunks - base : kWave);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[lane][k] = next[k];
+    fetch(c + kWave);
+    __syncthreads();
+    if (lane < 4) {
+#pragma unroll 4
+      for (int i = 0; i < n; ++i) {
+        const double nc = carry + t[i][lane];
+        t[i][lane] = carry;
+        carry = nc - floor(nc);
+      }
+    }
+    __syncthreads();
+    if (c < nchunks) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cr[4 * c + k] = t[lane][k];
+    }
+    __syncthreads();                     // t is read before the next chunks' sums
+  }
+}
+
 // Mix mode 1: y <- y / max(1, max |y|) per voice.  One 256-thread workgroup per voice.
 __global__ void __launch_bounds__(256) peak_normalise_kernel(const RenderArgs a) {
   __shared__ float red[256];
@@ -412,6 +546,15 @@ hipError_t launch_render(const RenderArgs& a, int runs_per_segment, bool clamp, 
 
 template <int RPS, bool CLAMP>
 hipError_t carries_rps(const RenderArgs& a, double* carries, int64_t stride, hipStream_t s) {
+  if (stride > kLongChunks && a.batch <= kLongVoices) {
+    const dim3 grid((unsigned)((stride + kCarryWaves - 1) / kCarryWaves), (unsigned)a.batch);
+    const dim3 block(kWave * kCarryWaves);
+    hipLaunchKernelGGL((long_carry_sums_kernel<RPS, CLAMP, 0>), grid, block, 0, s, a, carries, stride);
+    hipLaunchKernelGGL((long_carry_sums_kernel<RPS, CLAMP, 1>), grid, block, 0, s, a, carries, stride);
+    hipLaunchKernelGGL(long_carry_scan_kernel, dim3((unsigned)a.batch), dim3(kWave), 0, s, a, carries,
+                       stride);
+    return hipGetLastError();
+  }
   const int waves = stride < kCarryWaves ? (int)stride : kCarryWaves;
   hipLaunchKernelGGL((voice_carries_kernel<RPS, CLAMP>), dim3((unsigned)a.batch), dim3(kWave * waves),
                      0, s, a, carries, stride);
