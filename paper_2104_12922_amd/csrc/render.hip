@@ -281,7 +281,15 @@ __global__ void __launch_bounds__(kWave) render_kernel(const RenderArgs a) {
   const int64_t nitems = a.batch * per;
   for (int64_t item = blockIdx.x; item < nitems; item += gridDim.x) {
     const int64_t k = item / per;
-    const int part = (int)(item % per);
+    int part = (int)(item - k * per);
+    if (per % 2 == 0) {
+      // an even number of parts starts one further with every voice: with the
+      // same part of every voice on the same CUs (powers of two in number), those
+      // with the notes' silent ends are idle (512 voices of 64 chunks, a part
+      // each: 367 -> 335 us; an odd number spreads by itself)
+      part += (int)(k % per);
+      if (part >= per) part -= per;
+    }
     const int64_t b = a.order ? (int64_t)a.order[k] : k;
     if (b >= 0 && b < a.batch)
       render_item<RPS, CLAMP>(a, b, part / a.pass_split, part % a.pass_split, sh, tile);

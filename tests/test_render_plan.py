@@ -1,7 +1,8 @@
 """The render's default launch plan (host arithmetic, compiled from its header):
 a chunk's passes are split only while the chip has fewer than two workgroups per
 CU (512), never into more parts than there are passes, and never where the split
-parts would walk carries."""
+parts would walk carries; with carries, a voice is split into its chunks or not at
+all."""
 import os
 import shutil
 import subprocess
@@ -47,7 +48,9 @@ def test_plans(plans):
         chunks, passes = -(-J // 62), -(-J // 16)
         what = (batch, n, carried, slices, split)
         assert rps == 4 and 1 <= slices <= chunks and split in (1, 2, 4), what
-        if not carried:
+        if carried:
+            assert slices == (chunks if batch < 2048 else 1), what
+        else:
             assert slices <= max(1, chunks // 4), what
         if split > 1:
             assert (split // 2) * batch * slices < 512 and split // 2 < passes, what
