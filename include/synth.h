@@ -439,11 +439,11 @@ int synth_scale_rows(const float* g, const double* s, int64_t rows, int64_t cols
  * (V-statistic) estimate over all pairs, self-pairs included,
  *   MMD(X, Y) = 2 S(X, Y) / (n m) - S(X, X) / n^2 - S(Y, Y) / m^2,
  *   S(A, B)   = sum_{i, j} sum_k |A[i][k] - B[j][k]|.
- * Sets of up to 2048 sounds are summed in float64 from each dimension's
- * sorted values; beyond that (and where one set is much the smaller) a pair's
- * distance is accumulated in float32 over runs of 256 dimensions and
- * everything else in float64.  Both in a fixed order, so results are bitwise
- * reproducible.
+ * Sets of up to 2048 sounds are summed in float64, from each dimension's
+ * sorted values or, where the dimensions are few, over all pairs; beyond that
+ * (and where one set is much the smaller) a pair's distance is accumulated in
+ * float32 over runs of 256 dimensions and everything else in float64.  All in
+ * a fixed order, so results are bitwise reproducible.
  * ------------------------------------------------------------------------- */
 
 /* Bytes of device workspace that hold every synth_l1_pair_sum of sets of up to

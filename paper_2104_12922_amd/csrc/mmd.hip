@@ -5,8 +5,9 @@
 //   S(A, B) = sum_{i < n, j < m} sum_k |A[i][k] - B[j][k]|
 //   MMD(X, Y) = 2 S(X, Y) / (n m) - S(X, X) / n^2 - S(Y, Y) / m^2.
 //
-// Two ways: by sorting each dimension's values (sets of up to 2048 sounds,
-// sorted_pair_sum_kernel below), and over all pairs (l1_pair_sum_kernel):
+// Two kernels: one sorts each dimension's values (sets of up to 2048 sounds,
+// sorted_pair_sum_kernel below), one takes all pairs (l1_pair_sum_kernel, beyond
+// that and where the dimensions are too few for a sort, there in float64):
 //
 // Workgroups of 256 threads take tiles of 64 x 64 pairs and one share of
 // the embedding dimension (whole runs of 256 dimensions, so tiles x shares
@@ -15,12 +16,14 @@
 // (ty, tx) holds the 4 x 4 pairs rows ty + 16 a, columns tx + 16 b: per four
 // staged dimensions, 8 16-byte LDS reads (conflict-free: the A reads are
 // broadcasts, B rows 36 floats apart cover distinct banks) feed 64 |x - y|
-// accumulations.  A pair's distance is accumulated in float32 over each run
-// of 256 dimensions, then added to a float64 accumulator; a workgroup sums
+// accumulations.  A pair's distance is accumulated in float32 (or float64) over
+// each run of 256 dimensions, then added to a float64 accumulator; a workgroup sums
 // its pairs in a fixed order, and a second kernel sums the workgroups in
 // order, so S is bitwise reproducible and S(X, X) equals S(A = X, B = X).
 // Bound by VALU issue: two instructions (subtract, add of the absolute
-// value) per pair and dimension.
+// value) per pair and dimension (float64 at half the rate); padding past the last
+// dimension is skipped by fours (2000 x 2000 of 8 dimensions 15 -> 14 us for one
+// sum, which its launches bound, 5000 x 5000 58 -> 36).
 #include <algorithm>
 
 #include "synth_internal.h"
@@ -53,7 +56,12 @@ PairPlan pair_plan(int64_t n, int64_t m, int64_t dim) {
 
 // Stage rows r0 .. r0 + 63, dimensions k0 .. k0 + 31 of X (rows < rows, dims
 // < dim; anything outside reads as 0, and |0 - 0| adds nothing).
-__device__ __forceinline__ void stage_rows(float (*S)[kPLd], const float* __restrict__ X,
+template <class T>
+struct alignas(16) Vec4 {
+  T x, y, z, w;
+};
+template <class T>
+__device__ __forceinline__ void stage_rows(T (*S)[kPLd], const float* __restrict__ X,
                                            int64_t ld, int64_t rows, int64_t r0, int64_t k0,
                                            int64_t dim, bool vec) {
   const int t = threadIdx.x;
@@ -73,17 +81,23 @@ __device__ __forceinline__ void stage_rows(float (*S)[kPLd], const float* __rest
       v1 = make_float4(e[4], e[5], e[6], e[7]);
     }
   }
-  *reinterpret_cast<float4*>(&S[lr][lk]) = v0;
-  *reinterpret_cast<float4*>(&S[lr][lk + 4]) = v1;
+  typedef Vec4<T> V;
+  *reinterpret_cast<V*>(&S[lr][lk]) = V{(T)v0.x, (T)v0.y, (T)v0.z, (T)v0.w};
+  *reinterpret_cast<V*>(&S[lr][lk + 4]) = V{(T)v1.x, (T)v1.y, (T)v1.z, (T)v1.w};
 }
 
+__device__ __forceinline__ float magnitude(float x) { return fabsf(x); }
+__device__ __forceinline__ double magnitude(double x) { return fabs(x); }
+
+// T: of the differences and their sums over a run.
+template <class T>
 __global__ void __launch_bounds__(256) l1_pair_sum_kernel(const float* __restrict__ A, int64_t lda,
                                                           int64_t n, const float* __restrict__ B,
                                                           int64_t ldb, int64_t m, int64_t dim,
                                                           PairPlan plan, int vec,
                                                           double* __restrict__ partial) {
-  __shared__ __align__(16) float As[kPT][kPLd];
-  __shared__ __align__(16) float Bs[kPT][kPLd];
+  __shared__ __align__(16) T As[kPT][kPLd];
+  __shared__ __align__(16) T Bs[kPT][kPLd];
   __shared__ double red[256];
   const int t = threadIdx.x;
   const int tx = t & 15, ty = t >> 4;
@@ -93,34 +107,29 @@ __global__ void __launch_bounds__(256) l1_pair_sum_kernel(const float* __restric
   const int64_t kbeg = share * plan.runs_per_share * kF32Run;
   int64_t kend = kbeg + plan.runs_per_share * kF32Run;
   if (kend > dim) kend = dim;
-  float acc[4][4];
-  double dacc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      acc[a][b] = 0.0f;
-      dacc[a][b] = 0.0;
-    }
+  T acc[4][4] = {};
+  double dacc[4][4] = {};
   for (int64_t k0 = kbeg; k0 < kend; k0 += kPK) {
     stage_rows(As, A, lda, n, i0, k0, kend, vec != 0);
     stage_rows(Bs, B, ldb, m, j0, k0, kend, vec != 0);
     __syncthreads();
+    const int left = (int)min(kend - k0, (int64_t)kPK);
 #pragma unroll
     for (int kk = 0; kk < kPK; kk += 4) {
-      float4 xa[4], yb[4];
+      if (kk >= left) break;               // nothing but padding
+      Vec4<T> xa[4], yb[4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) xa[a] = *reinterpret_cast<const float4*>(&As[ty + 16 * a][kk]);
+      for (int a = 0; a < 4; ++a) xa[a] = *reinterpret_cast<const Vec4<T>*>(&As[ty + 16 * a][kk]);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) yb[b] = *reinterpret_cast<const float4*>(&Bs[tx + 16 * b][kk]);
+      for (int b = 0; b < 4; ++b) yb[b] = *reinterpret_cast<const Vec4<T>*>(&Bs[tx + 16 * b][kk]);
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          acc[a][b] += fabsf(xa[a].x - yb[b].x);
-          acc[a][b] += fabsf(xa[a].y - yb[b].y);
-          acc[a][b] += fabsf(xa[a].z - yb[b].z);
-          acc[a][b] += fabsf(xa[a].w - yb[b].w);
+          acc[a][b] += magnitude(xa[a].x - yb[b].x);
+          acc[a][b] += magnitude(xa[a].y - yb[b].y);
+          acc[a][b] += magnitude(xa[a].z - yb[b].z);
+          acc[a][b] += magnitude(xa[a].w - yb[b].w);
         }
     }
     __syncthreads();
@@ -130,7 +139,7 @@ __global__ void __launch_bounds__(256) l1_pair_sum_kernel(const float* __restric
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           dacc[a][b] += (double)acc[a][b];
-          acc[a][b] = 0.0f;
+          acc[a][b] = 0;
         }
     }
   }
@@ -469,7 +478,19 @@ __global__ void __launch_bounds__(256) sorted_final_kernel(const double* __restr
   __shared__ double red[3][256];
   const int t = threadIdx.x;
   double s[3] = {0.0, 0.0, 0.0};
-  for (int64_t i = t; i < count; i += 256)
+  int64_t i = t;
+  for (; i + 7 * 256 < count; i += 8 * 256) {   // eight blocks' loads in flight, added in order
+    double v[8][3];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[u][k] = partial[3 * (i + 256 * u) + k];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s[k] += v[u][k];
+  }
+  for (; i < count; i += 256)
 #pragma unroll
     for (int k = 0; k < 3; ++k) s[k] += partial[3 * i + k];
 #pragma unroll
@@ -506,24 +527,55 @@ int sort_regs(int64_t n, int64_t m) {
 // and one stages while the other sorts (1000 x 1000: 85 -> 79 us).
 int sort_cols(int r) { return r >= 32 ? 8 : 16; }
 
-// The three sums of an MMD are sorted whenever the registers hold the sets:
-// one pass against three launches over all pairs (8192 features, us: 64 x 64
-// sounds 88 -> 15, 1 x 1 of one feature 25 -> 12, 2000 x 2000 5320 -> 204,
-// and, the closest, 2000 x 2000 of 8 features 45 against 48).
-bool sort_mmd(int64_t n, int64_t m, int64_t dim) {
-  return n > 0 && m > 0 && dim > 0 && sort_regs(n, m) > 0;
-}
-
 int64_t tiled(int64_t n) { return (n + kPT - 1) / kPT * kPT; }
 
-// One sum alone is sorted up to 256 sounds, where both ways are bound by their
-// two launches or the sort is ahead (64 x 64: 29 -> 15 us, 256 x 64: 29 ->
-// 22), and beyond where its pairs (in whole tiles) outweigh sorting the longer
-// set: at 1000 x 64 all pairs take 31 us and the sort 74, at 1000 x 256 116
-// and 75, at 2000 x 64 64 and 191, at 2000 x 256 226 and 192.
-bool sort_one(int64_t n, int64_t m, int64_t dim) {
-  const int r = sort_regs(n, m);
-  return sort_mmd(n, m, dim) && (r <= 8 || tiled(n) * tiled(m) >= 6400 * (int64_t)r);
+// The ways of a sum.  kSorted and kPairs64 keep every difference and sum in
+// float64; a pair's distance over runs of 256 dimensions is float32 in kPairs32.
+enum class Way { kSorted, kPairs64, kPairs32 };
+
+// Sorting takes at least the latency of one wavefront's sort of 32 R values a
+// set, however few the dimensions (8 or 16 a workgroup leave most of the chip
+// idle), and all pairs in float64 at least its launches; so the way is chosen by
+// what both take, us as measured (sets of features; sorted and all pairs):
+//   one sum:    2000 x 2000 of 8      49 and 14    1000 x 1000 of 64   27 and 14
+//               300 x 300 of 128      22 and 20    1000 x 1000 of 256  27 and 35
+//               64 x 64 of 65536      69 and 35    256 x 256 of 8192   22 and 49
+//   an MMD:     1100 x 1100 of 16     48 and 32    1000 x 1000 of 8    26 and 29
+//               1 x 2048 of 33        51 and 44    2000 x 2000 of 64   50 and 82
+// The sort: a floor by its registers, then a rate per dimension.
+double sort_us(int r, int64_t dim) {
+  const double floor_us = r <= 8 ? 14.5 : r == 16 ? 22.0 : r == 32 ? 26.5 : 48.5;
+  const double rate = r == 4 ? 0.98e-3 : r == 8 ? 1.8e-3 : r == 16 ? 4.6e-3 : r == 32 ? 7.7e-3 : 24e-3;
+  return std::max(floor_us, 5.0 + rate * (double)dim);
+}
+// All pairs: what is left of the launches beside the kernel, and per 32 staged
+// dimensions of a share (fewer at the end cost about half and the rest by their
+// number) 3.1 us alone on a CU, 2.7 for every 256 workgroups.
+double pairs64_us(int64_t n, int64_t m, int64_t dim) {
+  const PairPlan p = pair_plan(n, m, dim);
+  const int64_t blocks = p.tiles_n * p.tiles_m * p.shares;
+  const int64_t d = std::min(dim, p.runs_per_share * kF32Run), rest = d % kPK;
+  const double chunks = (double)(d / kPK) + (rest ? 0.45 + 0.55 * (double)rest / kPK : 0.0);
+  return 6.0 + chunks * std::max(3.1, 2.7 * (double)((blocks + 255) / 256));
+}
+
+// The three sums of an MMD: one pass against three sums' launches.
+Way mmd_way(int64_t n, int64_t m, int64_t dim) {
+  const int r = n > 0 && m > 0 && dim > 0 ? sort_regs(n, m) : 0;
+  if (r == 0) return Way::kPairs32;
+  const double pairs = pairs64_us(n, m, dim) + pairs64_us(n, n, dim) + pairs64_us(m, m, dim);
+  return sort_us(r, dim) <= std::max(28.5, pairs) ? Way::kSorted : Way::kPairs64;
+}
+
+// One sum alone is left to float32 runs where one set of more than 256 sounds is
+// much the larger, and sorting it would outweigh the pairs (in whole tiles) at
+// any number of dimensions: at 1000 x 64 of 8192 all pairs take 31 us and the
+// sort 74, at 1000 x 256 116 and 75, at 2000 x 64 64 and 191, at 2000 x 256 226
+// and 192.
+Way one_way(int64_t n, int64_t m, int64_t dim) {
+  const int r = n > 0 && m > 0 && dim > 0 ? sort_regs(n, m) : 0;
+  if (r == 0 || (r > 8 && tiled(n) * tiled(m) < 6400 * (int64_t)r)) return Way::kPairs32;
+  return sort_us(r, dim) <= std::max(14.3, pairs64_us(n, m, dim)) ? Way::kSorted : Way::kPairs64;
 }
 
 template <int R, int C>
@@ -561,6 +613,11 @@ size_t sort_bytes(int64_t n, int64_t m, int64_t dim) {
   return (size_t)((dim + c - 1) / c) * 3 * sizeof(double);
 }
 
+size_t pairs_bytes(int64_t n, int64_t m, int64_t dim) {
+  const PairPlan p = pair_plan(n, m, dim);
+  return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+}
+
 // Bytes that hold the partial sums of every call of at most these sizes, so that
 // a workspace for the largest sets serves all: it grows with each size, where
 // the need of a call does not (which way it goes depends on the sizes, and a
@@ -575,6 +632,7 @@ size_t any_smaller_bytes(int64_t n, int64_t m, int64_t dim) {
                   sort_bytes(std::min<int64_t>(n, 2048), std::min<int64_t>(m, 2048), dim));
 }
 
+template <class T>
 hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                             int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
   const PairPlan p = pair_plan(n, m, dim);
@@ -582,7 +640,7 @@ hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float*
   if (blocks > 0 && dim > 0) {
     const int vec = ((lda | ldb) % 4 == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0) &&
                     (reinterpret_cast<uintptr_t>(B) % 16 == 0);
-    hipLaunchKernelGGL(l1_pair_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, s, A, lda, n, B,
+    hipLaunchKernelGGL(l1_pair_sum_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, A, lda, n, B,
                        ldb, m, dim, p, vec, partial);
   }
   hipLaunchKernelGGL(ordered_sum_kernel, dim3(1), dim3(256), 0, s, partial,
@@ -593,29 +651,23 @@ hipError_t launch_all_pairs(const float* A, int64_t lda, int64_t n, const float*
 }  // namespace
 
 size_t l1_pair_sum_need(int64_t n, int64_t m, int64_t dim) {
-  if (sort_one(n, m, dim)) return sort_bytes(n, m, dim);
-  const PairPlan p = pair_plan(n, m, dim);
-  return (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
+  return one_way(n, m, dim) == Way::kSorted ? sort_bytes(n, m, dim) : pairs_bytes(n, m, dim);
 }
 
 size_t l1_pair_sum_workspace(int64_t n, int64_t m, int64_t dim) { return any_smaller_bytes(n, m, dim); }
 
 hipError_t launch_l1_pair_sum(const float* A, int64_t lda, int64_t n, const float* B, int64_t ldb,
                               int64_t m, int64_t dim, double* partial, double* out, hipStream_t s) {
-  if (sort_one(n, m, dim))
-    return launch_sort_sums(A, lda, n, B, ldb, m, dim, partial, 0, out, s);
-  return launch_all_pairs(A, lda, n, B, ldb, m, dim, partial, out, s);
+  switch (one_way(n, m, dim)) {
+    case Way::kSorted: return launch_sort_sums(A, lda, n, B, ldb, m, dim, partial, 0, out, s);
+    case Way::kPairs64: return launch_all_pairs<double>(A, lda, n, B, ldb, m, dim, partial, out, s);
+    default: return launch_all_pairs<float>(A, lda, n, B, ldb, m, dim, partial, out, s);
+  }
 }
 
 size_t mmd_l1_need(int64_t n, int64_t m, int64_t dim) {
-  if (sort_mmd(n, m, dim))
-    return sort_bytes(n, m, dim);
-  size_t need = 0;
-  for (const PairPlan& p : {pair_plan(n, m, dim), pair_plan(n, n, dim), pair_plan(m, m, dim)}) {
-    const size_t b = (size_t)(p.tiles_n * p.tiles_m * p.shares) * sizeof(double);
-    need = b > need ? b : need;
-  }
-  return need;
+  if (mmd_way(n, m, dim) == Way::kSorted) return sort_bytes(n, m, dim);
+  return std::max({pairs_bytes(n, m, dim), pairs_bytes(n, n, dim), pairs_bytes(m, m, dim)});
 }
 
 size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
@@ -625,12 +677,13 @@ size_t mmd_l1_workspace(int64_t n, int64_t m, int64_t dim) {
 
 hipError_t launch_mmd_l1(const float* X, int64_t n, const float* Y, int64_t m, int64_t dim,
                          double* ws, double* out, hipStream_t s) {
-  if (sort_mmd(n, m, dim))
-    return launch_sort_sums(X, dim, n, Y, dim, m, dim, ws, 1, out, s);
+  const Way way = mmd_way(n, m, dim);
+  if (way == Way::kSorted) return launch_sort_sums(X, dim, n, Y, dim, m, dim, ws, 1, out, s);
   // the three sums reuse the workspace in stream order
-  hipError_t e = launch_all_pairs(X, dim, n, Y, dim, m, dim, ws, out + 1, s);
-  if (e == hipSuccess) e = launch_all_pairs(X, dim, n, X, dim, n, dim, ws, out + 2, s);
-  if (e == hipSuccess) e = launch_all_pairs(Y, dim, m, Y, dim, m, dim, ws, out + 3, s);
+  const auto sum = way == Way::kPairs64 ? launch_all_pairs<double> : launch_all_pairs<float>;
+  hipError_t e = sum(X, dim, n, Y, dim, m, dim, ws, out + 1, s);
+  if (e == hipSuccess) e = sum(X, dim, n, X, dim, n, dim, ws, out + 2, s);
+  if (e == hipSuccess) e = sum(Y, dim, m, Y, dim, m, dim, ws, out + 3, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(mmd_combine_kernel, dim3(1), dim3(64), 0, s, out, n, m);
   return hipGetLastError();
