@@ -6,8 +6,8 @@
 //
 // Three kernels (launch_gemm_bf16 chooses): whole-K tiles
 // (gemm_bf16_whole_kernel), few rows (gemm_bf16_few_kernel), and for the rest
-// (few tiles over a long K, operands without 16-byte rows, the log-mel
-// epilogues) the split-K kernel with its partial sums:
+// (few tiles over a long K, few columns over a short one, operands without
+// 16-byte rows, the log-mel epilogues) the split-K kernel with its partial sums:
 //
 // Tiles of 128 x 128 x 32 per 256-thread workgroup (four wavefronts in 2 x 2,
 // each 64 x 64 as 2 x 2 MFMA 32 x 32 blocks).  Tiles are staged in LDS as
@@ -960,6 +960,13 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, int a_op, int b_op, hipStream_t s
       e = hipGetLastError();
       return e != hipSuccess || groups == 1 ? e : launch_reduce(g, s);
     }
+    const int64_t t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    // Up to 32 columns and a short K over more than a tile a CU: whole tiles, one
+    // workgroup a CU, have nothing to hide their loads and stores behind; the split
+    // kernel has four (1000000 x 16, us, whole and split: K = 32 140 and 94, 64 141
+    // and 124, 128 172 and 188; K-major 262144 x 32 x 96 45 and 42, row-major 46
+    // and 46; 20000 rows 8.3 and 9).
+    const bool narrow = g.N <= 32 && g.K <= (a_op == kOpKMajor ? 96 : 64) && t128 > 256;
     // 256 x 128 tiles where they fill the chip and K is more than their
     // longer prologue (1024 x 8192 x 4096: 106 -> 81 us against 128 x 128);
     // 128 x 128 from where 64 x 64 ones would need a second round (0.7 us a
@@ -967,8 +974,8 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, int a_op, int b_op, hipStream_t s
     // idle for all of it: those keep to the split kernel (MLP forward of 333
     // rows: 65 us split, 77 whole; 512 rows: 88 and 70).
     if (t256 >= 192 && g.K > 512) return launch_whole_ops<2, 2, 4, 2, 3>(g, a_op, b_op, a16, s);
-    if (t64 > 256) return launch_whole_ops<2, 1, 2, 4, 4>(g, a_op, b_op, a16, s);
-    if (split == 1 || t64 >= (g.K > 2048 ? 128 : 64))
+    if (t64 > 256 && !narrow) return launch_whole_ops<2, 1, 2, 4, 4>(g, a_op, b_op, a16, s);
+    if (!narrow && (split == 1 || t64 >= (g.K > 2048 ? 128 : 64)))
       return launch_whole_ops<1, 1, 2, 2, 8>(g, a_op, b_op, a16, s);
   }
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
