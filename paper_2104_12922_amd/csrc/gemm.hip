@@ -5,9 +5,10 @@
 // X[r * ld + k]) and kOpRowMajorMN (X[k * ld + r]).
 //
 // Three kernels (launch_gemm_bf16 chooses): whole-K tiles
-// (gemm_bf16_whole_kernel), few rows (gemm_bf16_few_kernel), and for the rest
-// (few tiles over a long K, few columns over a short one, operands without
-// 16-byte rows, the log-mel epilogues) the split-K kernel with its partial sums:
+// (gemm_bf16_whole_kernel; over a very long K its parts side by side, with
+// partial sums), few rows (gemm_bf16_few_kernel), and for the rest (few tiles
+// over a long K, few columns over a short one, operands without 16-byte rows, the
+// log-mel epilogues) the split-K kernel with its partial sums:
 //
 // Tiles of 128 x 128 x 32 per 256-thread workgroup (four wavefronts in 2 x 2,
 // each 64 x 64 as 2 x 2 MFMA 32 x 32 blocks).  Tiles are staged in LDS as
@@ -603,7 +604,9 @@ __device__ __forceinline__ void wait_loads() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
 }
 
-template <int AOP, int BOP, int MB, int NB, int WM, int WN, int NS, bool AANY>
+// PARTS: the parts of the sum are spread over grid.y, a run of them to each
+// workgroup, and every part's product goes to g.partial for the split reduction.
+template <int AOP, int BOP, int MB, int NB, int WM, int WN, int NS, bool AANY, bool PARTS>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2, 2)))
     gemm_bf16_whole_kernel(GemmArgs g) {
   constexpr int TM = 32 * MB * WM, TN = 32 * NB * WN, NW = WM * WN;
@@ -618,18 +621,25 @@ __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_
   const int64_t id = (nblk % 8 == 0) ? (int64_t)(blockIdx.x % 8) * (nblk / 8) + blockIdx.x / 8
                                      : (int64_t)blockIdx.x;
   const int64_t m0 = id / tiles_n * TM, n0 = id % tiles_n * TN;
-  const int K = (int)g.K;
   const int split = g.split > 1 ? g.split : 1;
   const int kper = (int)(((g.K + split - 1) / split + BK - 1) / BK * BK);
+  // this workgroup's parts, their first k and (K) their end
+  const int run = PARTS ? (split + (int)gridDim.y - 1) / (int)gridDim.y : split;
+  const int p0 = PARTS ? (int)blockIdx.y * run : 0, p1 = min(split, p0 + run);
+  const int k0 = (int)min(g.K, (int64_t)p0 * kper), K = (int)min(g.K, (int64_t)p1 * kper);
 
   Stager<AOP, TM, NW, AANY> sa;
   Stager<BOP, TN, NW, false> sb;
   sa.init(g.A, g.lda, m0, g.M, tile[0]);
   sb.init(g.B, g.ldb, n0, g.N, tile[0] + TM * SK);
+  if constexpr (PARTS) {
+    sa.ptr += 2 * (AOP == kOpKMajor ? (int64_t)1 : g.lda) * k0;
+    sb.ptr += 2 * (BOP == kOpKMajor ? (int64_t)1 : g.ldb) * k0;
+  }
   f32x16 sum[MB][NB] = {};
   // the stage to load next, NS - 1 ahead of the one computed: its k, its
   // part's end and its buffer
-  int lk = 0, lend = min(kper, K), lbuf = 0;
+  int lk = k0, lend = min(k0 + kper, K), lbuf = 0;
   auto load_next = [&]() {
     if (lk >= K) return;
     const int left = lend - lk;
@@ -671,9 +681,9 @@ __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_
   next_stage(lk < K);
   read(0, 0, 0);
   int buf = 0;
-  for (int kbeg = 0; kbeg < K; kbeg += kper) {
+  for (int p = p0; p < p1; ++p) {
     f32x16 acc[MB][NB] = {};
-    for (int left = min(kper, K - kbeg); left > 0; left -= SK) {
+    for (int left = min((int64_t)kper, K - (int64_t)p * kper); left > 0; left -= SK) {
       const int nbuf = buf + 1 < NS ? buf + 1 : 0;
 #pragma unroll
       for (int q = 0; q < SK / 16; ++q) {
@@ -697,8 +707,20 @@ __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) sum[i][j] += acc[i][j];
+      for (int j = 0; j < NB; ++j) {
+        if constexpr (PARTS) {
+          const int64_t col = n0 + (wn * NB + j) * 32 + (lane & 31);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int64_t row = m0 + (wm * MB + i) * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+            if (col < g.N && row < g.M) g.partial[(p * g.M + row) * g.N + col] = acc[i][j][v];
+          }
+        } else {
+          sum[i][j] += acc[i][j];
+        }
+      }
   }
+  if constexpr (PARTS) return;
   // the sums to LDS (the last stage's reads are over behind the barrier)
   static_assert(sizeof(tile) >= TM * TN * sizeof(float), "the staging buffers hold the sums");
   __syncthreads();
@@ -897,12 +919,22 @@ hipError_t launch_whole(const GemmArgs& g, bool a16, hipStream_t s) {
   const int64_t tiles = ((g.M + TM - 1) / TM) * ((g.N + TN - 1) / TN);
   if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (a16)
-    hipLaunchKernelGGL((gemm_bf16_whole_kernel<AOP, BOP, MB, NB, WM, WN, NS, false>),
+    hipLaunchKernelGGL((gemm_bf16_whole_kernel<AOP, BOP, MB, NB, WM, WN, NS, false, false>),
                        dim3((unsigned)tiles), dim3(64 * WM * WN), 0, s, g);
   else
-    hipLaunchKernelGGL((gemm_bf16_whole_kernel<AOP, BOP, MB, NB, WM, WN, NS, true>),
+    hipLaunchKernelGGL((gemm_bf16_whole_kernel<AOP, BOP, MB, NB, WM, WN, NS, true, false>),
                        dim3((unsigned)tiles), dim3(64 * WM * WN), 0, s, g);
   return hipGetLastError();
+}
+
+// 128 x 128 tiles of K-major operands, the parts spread over `groups` workgroups
+// a tile, then their sum.
+hipError_t launch_parts(const GemmArgs& g, int groups, hipStream_t s) {
+  const int64_t tiles = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+  hipLaunchKernelGGL((gemm_bf16_whole_kernel<kOpKMajor, kOpKMajor, 2, 1, 2, 4, 4, false, true>),
+                     dim3((unsigned)tiles, (unsigned)groups), dim3(512), 0, s, g);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_reduce(g, s);
 }
 
 template <int... T>
@@ -915,6 +947,8 @@ hipError_t launch_whole_ops(const GemmArgs& g, int a_op, int b_op, bool a16, hip
 }
 
 }  // namespace
+
+constexpr int64_t kLongK = 12288, kFewWork = (int64_t)1 << 20;   // see launch_gemm_bf16
 
 // The number of parts a product's sum over K is taken in.  Each part starts
 // from zero and the parts are added in order, so the number is part of the
@@ -949,18 +983,25 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, int a_op, int b_op, hipStream_t s
     const int64_t t32 = ((g.M + 31) / 32) * ((g.N + 31) / 32);
     const int64_t t64 = ((g.M + 63) / 64) * ((g.N + 63) / 64);
     const int64_t t256 = ((g.M + 255) / 256) * ((g.N + 127) / 128);
+    const int64_t t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    const bool k_major = a_op == kOpKMajor && b_op == kOpKMajor && a16;
     // Few rows.  With more than 8 parts every 32 x 32 tile re-reads its
-    // operands over a long K: up to 128 tiles (MLP forward, us: 16 rows 45 ->
-    // 23, 128 rows 46 -> 44; 200 rows by this kernel 57, by the split one 40).
-    if (a_op == kOpKMajor && b_op == kOpKMajor && a16 && split > 1 &&
-        t32 <= (split > kFewWaves ? 128 : 512)) {
+    // operands over all of K: up to tiles x K of 2^20 (MLP forward, us: 16 rows 45
+    // -> 23, 128 rows 46 -> 44; 200 rows by this kernel 57, by the split one 40;
+    // of 16384 inputs 64 rows 51 -> 41, 128 rows by this kernel 59, split 50).
+    if (k_major && split > 1 && (split > kFewWaves ? t32 * g.K <= kFewWork : t32 <= 512)) {
       const int groups = (split + kFewWaves - 1) / kFewWaves;
       hipLaunchKernelGGL(gemm_bf16_few_kernel, dim3((unsigned)t32, (unsigned)groups),
                          dim3(64 * kFewWaves), 0, s, g);
       e = hipGetLastError();
       return e != hipSuccess || groups == 1 ? e : launch_reduce(g, s);
     }
-    const int64_t t128 = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+    // A long K over up to half as many tiles as CUs: its parts side by side
+    // (MLP forward of 65536 inputs, us, split kernel, whole tiles, parts: 512 rows
+    // 179, 339, 141; 1100 rows 551, 582, 284; of 16384 inputs 512 rows 86, 109,
+    // 73).  Below this line whole tiles are no slower than the split kernel was.
+    if (k_major && split > 1 && g.K >= kLongK && t128 <= 128)
+      return launch_parts(g, (int)(256 / t128 < split ? 256 / t128 : split), s);
     // Up to 32 columns and a short K over more than a tile a CU: whole tiles, one
     // workgroup a CU, have nothing to hide their loads and stores behind; the split
     // kernel has four (1000000 x 16, us, whole and split: K = 32 140 and 94, 64 141

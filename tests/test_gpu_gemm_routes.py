@@ -1,4 +1,5 @@
-"""The bf16 products at the lines between their kernels: few columns over a short K.
+"""The bf16 products at the lines between their kernels: a long K whose parts are
+taken side by side, few rows at the line of tiles x K, few columns over a short K.
 
 Small-integer operands keep every float32 sum exact (|sum| <= 9 K < 2^24), so
 those products must equal the integer product bit for bit."""
@@ -19,6 +20,22 @@ def L():
 
 def _ints(shape, g):
     return torch.randint(-3, 4, shape, generator=g).to(BF)
+
+
+@pytest.mark.parametrize("B,d_in,d_h", [(33, 12288, 1024), (129, 12296, 264), (130, 12280, 264),
+                                        (300, 20008, 200), (513, 12288, 1024), (1000, 16384, 136),
+                                        (64, 16384, 1024), (65, 16384, 1024), (2049, 12320, 1024)])
+def test_long_sums_are_exact(L, B, d_in, d_h):
+    g = torch.Generator().manual_seed(B + d_in)
+    z = lambda *s: torch.zeros(*s).numpy()
+    w1 = _ints((d_h, d_in), g)
+    net = L.MLP({"w1t": w1.float().numpy(), "b1": z(d_h), "w2t": z(d_h, d_h), "b2": z(d_h),
+                 "w3t": z(8, d_h), "b3": z(8)})
+    x = _ints((B, d_in), g)
+    net.forward(x.cuda())
+    ref = (x.cuda().float() @ w1.cuda().float().T).cpu()       # exact: integers below 2^24
+    assert torch.equal(ref[:3].double(), x[:3].double() @ w1.double().T)
+    assert torch.equal(net.a["h1pre"].cpu(), ref)
 
 
 @pytest.mark.parametrize("M", [32768, 32769 + 7, 70000])
