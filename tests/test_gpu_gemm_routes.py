@@ -1,5 +1,6 @@
 """The bf16 products at the lines between their kernels: a long K whose parts are
-taken side by side, few rows at the line of tiles x K, few columns over a short K.
+taken side by side, few rows at the line of tiles x K, few columns over a short K,
+and the MLP's output layer (78 columns) where its sigmoid is not saturated.
 
 Small-integer operands keep every float32 sum exact (|sum| <= 9 K < 2^24), so
 those products must equal the integer product bit for bit."""
@@ -49,3 +50,23 @@ def test_few_columns_are_exact(L, M, N, K, a_layout, b_layout):
                     (B.T if b_layout == 0 else B).contiguous().cuda(), M, N, K, a_layout, b_layout,
                     bias=bias.cuda())
     assert torch.equal(C.cpu(), A.float() @ B.float() + bias)
+
+
+@pytest.mark.parametrize("B", [1, 31, 33, 129, 300, 513])
+def test_mlp_output_layer(L, B):
+    """Logits of about 1, so that nearly every output tells of its sum: float32
+    sums of 1024 terms are within 1024 x 2^-24 of the sum of magnitudes, the
+    sigmoid passes at most a quarter of that on and its own arithmetic 2^-22."""
+    g = torch.Generator().manual_seed(B)
+    w = lambda o, i: (torch.randn(o, i, generator=g) / i ** 0.5).numpy()
+    net = L.MLP({"w1t": w(1024, 8192), "b1": torch.zeros(1024).numpy(), "w2t": w(1024, 1024),
+                 "b2": torch.zeros(1024).numpy(), "w3t": 2 * w(78, 1024),
+                 "b3": torch.randn(78, generator=g).numpy()})
+    net.forward(torch.randn(B, 8192, generator=g).to(BF).cuda())
+    h = net.a["h2"][:B].double()
+    w3 = net.wb["w3t"].double()
+    z = h @ w3.T.contiguous() + net.w["b3"].double()
+    mag = h.abs() @ w3.T.abs().contiguous() + net.w["b3"].double().abs()
+    out = net.a["out"][:B].double()
+    assert float((z.abs() < 4).double().mean()) > 0.95 and float(z.std()) > 0.5
+    assert bool(((torch.sigmoid(z) - out).abs() <= 0.25 * 1024 * 2.0 ** -24 * mag + 2.0 ** -22).all())
