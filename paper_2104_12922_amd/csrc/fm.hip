@@ -16,14 +16,17 @@
 // store instruction writes 1 KB of contiguous audio).  The four samples share
 // a control period; the phase n f_i / sr of the first is a whole number of
 // 2^-64 cycles that wraps by itself and advances by one 64-bit addition per
-// step (n 2^-64 cycles from the truncation of f_i / sr to that unit, against
+// step (off by at most n 2^-64 cycles from the truncation of f_i / sr to that unit, against
 // n f_i / sr 2^-53 from a float64 product), its upper half the float32 phase in
 // [0, 1] (2^-32 cycles); the next three add f_i / sr in float32 (within 2e-7
 // cycles), and the float32 hardware sine takes revolutions.  Periods after every envelope has reached 0 are zero-filled
-// without computation.  Bound by VALU issue: four sines (quarter rate) and 25
-// other instructions per sample (33 with a float64 product, floor and
-// conversion per operator and step, and each envelope's two values read and
-// subtracted there): 16384 voices of 1 .. 4 s 2045 -> 1869 us.
+// without computation.  Bound by VALU issue: four sines and about 25 other
+// instructions per sample, at five wavefronts per SIMD (91 registers; with the
+// operators' constants in vector registers 123 and four).  16384 voices of 1, 2
+// and 4 s: 1970 us with a float64 product, floor and conversion per operator and
+// step, 1790 with fixed-point phases and envelope pairs read as vectors, 1774 with
+// the constants formed by a lane each and kept in scalar registers; 65536 voices
+// of 500 samples 144, 164 and 128.
 #include "voice_device.h"
 
 namespace synth {
@@ -58,11 +61,20 @@ struct FmArgs {
   const int32_t* order;      // null, or the voices in the order workgroups take them
 };
 
+// Lane `from`'s value in a scalar register.
+__device__ __forceinline__ float of_lane(float x, int from) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), from));
+}
+__device__ __forceinline__ uint64_t of_lane(uint64_t x, int from) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(x >> 32), from) << 32 |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)x, from);
+}
+
 __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
   __shared__ double v[kFmParams];
   __shared__ double dv[kDerived];
   __shared__ __align__(16) float env0[64][4], envd[64][4];   // per period: value at its start, slope
-  __shared__ __align__(16) float last[4];                    // value at the chunk's end
+  __shared__ __align__(16) float last[4];                    // value at the last chunk's end
   const int lane = threadIdx.x;
   const int64_t b = a.order ? (int64_t)a.order[blockIdx.x] : (int64_t)blockIdx.x;
   if (b < 0 || b >= a.batch) return;         // an order entry out of range renders nothing
@@ -92,12 +104,13 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
   }
   __syncthreads();
   const double note_off = v[1] * rc;
-  // operator constants (uniform)
+  // operator constants and the envelope's first value: lane i forms operator i's,
+  // the constants then go to scalar registers (formed by every lane for all four,
+  // 65536 voices of 100 samples took 127 us)
   uint64_t incx[4];                        // cycles per sample in units of 2^-64
   float lvl[4], incf[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int pb = kOpBase[i];
+  {
+    const int pb = kOpBase[0] + (kOpBase[1] - kOpBase[0]) * (lane & 3);
     const double f = 440.0 * voice::exp2_f64((v[0] - 69.0) / 12.0) * v[pb] *
                      voice::exp2_f64(v[pb + 1] / 1200.0);
     // limited from above only: whole cycles below -1/2 are taken out (exactly),
@@ -106,20 +119,25 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
     double inc = fmin(f, a.sr / 2.0) / a.sr;
     inc -= rint(inc);
     const uint64_t mag = (uint64_t)(fabs(inc) * 0x1p64);
-    incx[i] = inc < 0.0 ? 0 - mag : mag;
-    incf[i] = (float)inc;
-    lvl[i] = (float)v[pb + 2];
+    if (lane < 4) last[lane] = (float)v[pb + 2] * (float)adsr_value(dv, lane, 0.0, note_off);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      incx[i] = of_lane(inc < 0.0 ? 0 - mag : mag, i);
+      incf[i] = of_lane((float)inc, i);
+      lvl[i] = of_lane((float)v[pb + 2], i);
+    }
   }
+  __syncthreads();
   float nan0[4];                           // 0, or NaN for a frequency of minus infinity
 #pragma unroll
   for (int i = 0; i < 4; ++i) nan0[i] = 0.0f * incf[i];
-  const float m01 = (float)v[kModBase], m02 = (float)v[kModBase + 1], m03 = (float)v[kModBase + 2];
-  const float m12 = (float)v[kModBase + 3], m13 = (float)v[kModBase + 4];
-  const float m23 = (float)v[kModBase + 5];
+  const float m01 = of_lane((float)v[kModBase], 0), m02 = of_lane((float)v[kModBase + 1], 0);
+  const float m03 = of_lane((float)v[kModBase + 2], 0), m12 = of_lane((float)v[kModBase + 3], 0);
+  const float m13 = of_lane((float)v[kModBase + 4], 0), m23 = of_lane((float)v[kModBase + 5], 0);
   const double wsum = v[kMixBase] + v[kMixBase + 1] + v[kMixBase + 2] + v[kMixBase + 3];
   const double wn = 1.0 / fmax(1.0, wsum);
-  const float w0 = (float)(v[kMixBase] * wn), w1 = (float)(v[kMixBase + 1] * wn);
-  const float w2 = (float)(v[kMixBase + 2] * wn), w3 = (float)(v[kMixBase + 3] * wn);
+  const float w0 = of_lane((float)(v[kMixBase] * wn), 0), w1 = of_lane((float)(v[kMixBase + 1] * wn), 0);
+  const float w2 = of_lane((float)(v[kMixBase + 2] * wn), 0), w3 = of_lane((float)(v[kMixBase + 3] * wn), 0);
   // every envelope is exactly 0 from control sample note_off + R_i on; a
   // period whose two control values are 0 is silent
   double rel_end = 0.0;
@@ -145,8 +163,8 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
     // control values at j0 + 0 .. 64 (the last period holds its value): lane
     // l evaluates j0 + l + 1, the end of period l, and takes its start from
     // lane l - 1; the value at j0 is the previous chunk's last one (the same
-    // control sample).  Operator 0 modulates nothing: its mix weight is in its
-    // envelope.
+    // control sample; before the first chunk, the one at 0).  Operator 0
+    // modulates nothing: its mix weight is in its envelope.
     {
       const double jd = (double)min(j0 + lane + 1, J - 1);
       float r[4];
@@ -156,8 +174,7 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         l[i] = __shfl_up(r[i], 1);
-        if (lane == 0)
-          l[i] = j0 == 0 ? lvl[i] * (float)adsr_value(dv, i, 0.0, note_off) : last[i];
+        if (lane == 0) l[i] = last[i];
       }
       *reinterpret_cast<float4*>(env0[lane]) = make_float4(w0 * l[0], l[1], l[2], l[3]);
       *reinterpret_cast<float4*>(envd[lane]) =
@@ -168,7 +185,8 @@ __global__ void __launch_bounds__(64) fm_render_kernel(FmArgs a) {
     __syncthreads();
     uint64_t ph64[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ph64[i] = (uint64_t)(c0 + 4 * lane) * incx[i];
+    for (int i = 0; i < 4; ++i)
+      ph64[i] = (uint64_t)c0 * incx[i] + (uint64_t)(uint32_t)(4 * lane) * incx[i];
     for (int p = 4 * lane; p < cnt; p += 256) {
       // samples p .. p + 3 lie in one control period (q and p are multiples
       // of 4): one period index, one phase per operator, the other three
