@@ -663,13 +663,15 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
     const double unit = live ? 1.0 / rc : 0.0;
     const double later = wave_rev_excl_scan(dph, lane);
     const double df = live ? later / rc : 0.0;
-    env[2 + 2 * i][lane] = df * v[pb + 1];
-    tail[i] = unit * v[pb + 1];
+    env[2 + 2 * i][lane] = live ? df * v[pb + 1] : 0.0;
+    tail[i] = live ? unit * v[pb + 1] : 0.0;
     const int sl = kRowLfo + 12 * i;
-    emit4(S.part, sl, lane, df, df * erate, dph / kTwoPi, dw * ((1.0 + sn[i]) / 2.0 - lfo[i]));
-    emit4(S.part, sl + 4, lane, dw * (1.0 - fabs(2.0 * p - 1.0) - lfo[i]), dw * (p - lfo[i]),
-          dw * (1.0 - p - lfo[i]), dw * ((p < 0.5 ? 1.0 : 0.0) - lfo[i]));
-    emit4(S.part, sl + 8, lane, unit, unit * erate, dph, 0.0);
+    // what does not reach a parameter leaves it alone also where it is not finite
+    const double er = live ? erate : 0.0, lf = invW > 0.0 ? lfo[i] : 0.0;
+    emit4(S.part, sl, lane, df, df * er, dph / kTwoPi, dw * ((1.0 + sn[i]) / 2.0 - lf));
+    emit4(S.part, sl + 4, lane, dw * (1.0 - fabs(2.0 * p - 1.0) - lf), dw * (p - lf),
+          dw * (1.0 - p - lf), dw * ((p < 0.5 ? 1.0 : 0.0) - lf));
+    emit4(S.part, sl + 8, lane, unit, unit * er, dph, 0.0);
   }
   // ADSRs: derivatives per unit of the envelope's adjoint (0 where neither it
   // nor a later phase adjoint reaches the envelope)
@@ -679,6 +681,7 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
     const double de = own ? env[k][lane] : 0.0;
     const double tl = k == 2 ? tail[0] : k == 4 ? tail[1] : 0.0;
     double dA = 0.0, dD = 0.0, dS = 0.0, dR = 0.0, dO = 0.0, dal = 0.0;
+    bool live_a = false, live_d = false, live_r = false;   // ramps that the sample lies on
     if (de != 0.0 || tl != 0.0) {
       const double A = dv[kEnvA + k], D = dv[kEnvD + k], Rr = dv[kEnvR + k];
       const double iA = dv[kEnvInvA + k], iD = dv[kEnvInvD + k], iR = dv[kEnvInvR + k];
@@ -692,13 +695,16 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
       const double dPd = dM * (1.0 - Sus);
       dS = dM * (1.0 - Pd);
       dal = dPa * la + dPd * ld + dPr * lr;
-      if (ramp_live(jd, 0.0, A, iA)) dA += dPa * xa * (-jd * iA * iA);
-      if (ramp_live(jd, A, D, iD)) {
+      live_a = ramp_live(jd, 0.0, A, iA);
+      live_d = ramp_live(jd, A, D, iD);
+      live_r = ramp_live(jd, note_off, Rr, iR);
+      if (live_a) dA += dPa * xa * (-jd * iA * iA);
+      if (live_d) {
         const double dd = -dPd * xd;       // d/d dec
         dA += dd * (-iD);
         dD += dd * (-(jd - A) * iD * iD);
       }
-      if (ramp_live(jd, note_off, Rr, iR)) {
+      if (live_r) {
         const double dr = -dPr * xr;       // d/d rel
         dO += dr * (-iR);
         dR += dr * (-(jd - note_off) * iR * iR);
@@ -708,8 +714,10 @@ __global__ void __launch_bounds__(kWave, 3) adjoint_chunk_grad_kernel(const Rend
       dR *= rc;
       dO *= rc;
     }
-    goff += de * dO;
-    emit4(S.part, kRowEnv + 8 * k, lane, de * dA, de * dD, de * dS, de * dR);
+    // a ramp that is not passed takes no adjoint, also not one that is not finite
+    const double deA = live_a || live_d ? de : 0.0, deD = live_d ? de : 0.0, deR = live_r ? de : 0.0;
+    goff += deR * dO;
+    emit4(S.part, kRowEnv + 8 * k, lane, deA * dA, deD * dD, de * dS, deR * dR);
     emit4(S.part, kRowEnv + 8 * k + 4, lane, de * dal, tl * dal, tl * dO, 0.0);
     if (k == 2 || k == 4) emit4(S.part, kRowTail + 2 * k - 4, lane, tl * dA, tl * dD, tl * dS, tl * dR);
   }
@@ -752,7 +760,7 @@ __global__ void __launch_bounds__(kParamThreads) adjoint_params_kernel(const Ren
 #pragma unroll 4
       for (int64_t c = t.nchunks - 1; c >= 0; --c) {
         const double f = sum_of(p, c), d = sum_of(dp, c);
-        if (later != 0.0) s += later * f;
+        if (later != 0.0 && f != 0.0) s += later * f;
         later += d;
       }
     }
