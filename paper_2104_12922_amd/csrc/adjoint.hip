@@ -46,6 +46,8 @@ enum {
   kNumRed
 };
 
+constexpr double kIndexScale = 1024.0;           // no control period has more samples
+
 // sin and cos of 2 pi j / 256 from the quarter wave.
 __device__ __forceinline__ double2 sincos_entry(int j) {
   const int r = j & 63, o = j >> 6;              // octet pair: quarter o, offset r
@@ -248,11 +250,12 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
       const double A40d = __shfl(a40_d, src), A4dd = __shfl(a4d_d, src);
       const double p10 = A10d * L1d_2pi, p1d = A1dd * L1d_2pi;
       const double p30 = A30d * L2cg2pi, p3d = A3dd * L2cg2pi;
-      const float A30 = (float)A30d, A3d = (float)A3dd;
+      const float A30 = (float)A30d, A3d = (float)(A3dd * kIndexScale);
       double P1 = 0.0, P2 = 0.0;
       // sums over the run of l = inc and ks l, of both times P (float64), and
       // of d and ks d of the three amplitude terms, the shape and gain terms
-      // (float32 over at most q / RPS samples)
+      // (float32 over at most q / RPS samples; there ks counts 2^-10, exactly, as
+      // a period has at most 1024 samples, so that ks d overflows no earlier than d)
       double c1 = 0.0, k1 = 0.0, e1 = 0.0, f1 = 0.0, c2 = 0.0, k2 = 0.0, e2 = 0.0, f2 = 0.0;
       float s1 = 0.0f, w1 = 0.0f, s3 = 0.0f, w3 = 0.0f, s4 = 0.0f, w4 = 0.0f, fsh = 0.0f, fk = 0.0f;
       const int seg_valid = ls < nseg ? 1 : 0;
@@ -263,11 +266,11 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
       const uint16_t* tnl = tn + lane * h;
       auto run = [&](auto whole) {
         double kd = (double)(m * h);                 // sample index within the segment
-        float kf = (float)(m * h);
+        float kf = (float)(m * h) * (float)(1.0 / kIndexScale);
 #pragma unroll 1
         for (int k = 0; k < h; ++k) {
           const float gk = tgl[k];                   // 0 past the voice's end
-          const float nn = (float)tnl[k] - 32767.5f;
+          const float nn = fmaf((float)tnl[k], 0x1p-15f, -32767.5f * 0x1p-15f);   // exact
           const double gd = (double)gk;
           double sn1, cs1, sn2, cs2;
           sincos_table(sct, t1, sn1, cs1);
@@ -315,7 +318,7 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
           t1 += i1; i1 *= r1;
           t2 += i2; i2 *= r2;
           kd += 1.0;
-          kf += 1.0f;
+          kf += (float)(1.0 / kIndexScale);
         }
       };
       if (__all(nlive == h || !seg_valid)) run(std::true_type{});   // invalid lanes are not used
@@ -333,16 +336,17 @@ __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArg
       acc[kRC02] = c2 - acc[kRC12];
       acc[kRE12] = f2 * inv_q;
       acc[kRE02] = e2 - acc[kRE12];
-      const double L2cg = L2d * (double)cg, L3n = L3d * (1.0 / 32768.0);
-      acc[kRA11] = L1d * w1 * inv_q;
+      const double L2cg = L2d * (double)cg;
+      const double inv_qi = inv_q * kIndexScale;
+      acc[kRA11] = L1d * w1 * inv_qi;
       acc[kRA01] = L1d * s1 - acc[kRA11];
-      acc[kRA13] = L2cg * w3 * inv_q;
+      acc[kRA13] = L2cg * w3 * inv_qi;
       acc[kRA03] = L2cg * s3 - acc[kRA13];
-      acc[kRA14] = L3n * w4 * inv_q;
-      acc[kRA04] = L3n * s4 - acc[kRA14];
-      acc[kRL1] = A10d * s1 + A1dd * w1;
-      acc[kRL2] = (double)cg * (A30d * s3 + A3dd * w3);
-      acc[kRL3] = (A40d * s4 + A4dd * w4) * (1.0 / 32768.0);
+      acc[kRA14] = L3d * w4 * inv_qi;
+      acc[kRA04] = L3d * s4 - acc[kRA14];
+      acc[kRL1] = A10d * s1 + A1dd * kIndexScale * w1;
+      acc[kRL2] = (double)cg * (A30d * s3 + A3dd * kIndexScale * w3);
+      acc[kRL3] = A40d * s4 + A4dd * kIndexScale * w4;
       acc[kRShape] = L2d * fsh;
       acc[kRK] = 4.0 * L2cg * fk;
       // combine the RPS runs of each segment: E += P_before * C, then sums

@@ -1,13 +1,15 @@
-"""The render adjoint on cotangents and parameters that are not finite: an adjoint
-reaches only the parameters that the sample depends on (a ramp that is not passed,
-shape weights without a sum).  Against the float64 oracle."""
+"""The render adjoint on cotangents and parameters that are not finite or nearly
+as large as float32 goes: an adjoint reaches only the parameters that the sample
+depends on (a ramp that is not passed, shape weights without a sum), and a large
+one does not overflow before its sums do.  Against the float64 oracle, by the
+criterion of test_gpu_adjoint."""
 import numpy as np
 import pytest
 import torch
 
 import workloads as W
 from oracle import philox
-from test_gpu_adjoint import oracle_grad
+from test_gpu_adjoint import check, oracle_grad
 
 pytestmark = pytest.mark.gpu
 B = 6
@@ -55,3 +57,19 @@ def test_shape_weights_without_a_sum(S):
     u[:, 35] = np.nan                                   # a shape weight of the first LFO
     got = _grad(S, u, g, table)
     assert np.isfinite(got[:, 36:40]).all()
+
+
+@pytest.mark.parametrize("scale", [1e30, 1e37])
+@pytest.mark.parametrize("period", [100, 768])
+def test_large_cotangents(S, scale, period):
+    table = W.default_nebula().table()
+    N = 9 * period
+    u, g = _inputs(N)
+    g[np.arange(B), N - 1 - np.arange(B) * 37] = scale
+    rc = 44100.0 / period
+    got = S.synth_render_backward(torch.tensor(u, dtype=torch.float32).cuda(), torch.tensor(g).cuda(),
+                                  table, control_rate=rc).cpu().numpy()
+    assert not np.isnan(got).any()                      # (a pitch's gradient may itself pass 3.4e38)
+    if period == 100:
+        assert np.isfinite(got).all()
+        check(got, oracle_grad(u, g, N, table))
