@@ -42,8 +42,8 @@ RENDER_SLOTS_PER_SAMPLE = 38.0
 # from two rocprofv3 --pmc runs (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 KiB; the
 # factors make each counter read 1 GiB for a plain 1 GiB device copy).  Valid
 # only for the kernel sources with this digest; reported as null otherwise.
-RENDER_TRAFFIC = {"sources_sha256_16": "eaa3c071bc52b0a9",
-                  "fetch_bytes": 10993152, "write_bytes": 6758743633, "valu_busy": 0.93}
+RENDER_TRAFFIC = {"sources_sha256_16": "5f0a8dd452502391",
+                  "fetch_bytes": 11113267, "write_bytes": 6758901658, "valu_busy": 0.93}
 RENDER_SOURCES = ("render.hip", "voice_device.h", "philox.h", "series_tables.h")
 
 

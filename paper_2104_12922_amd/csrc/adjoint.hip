@@ -117,14 +117,17 @@ __device__ __forceinline__ int64_t silent_chunk(const double* v, double rc) {
   return (js + kSegsPerChunk - 1) / kSegsPerChunk;
 }
 
-// Bound by float64 VALU issue at two wavefronts per SIMD: 125 instructions a
-// sample, 92 of them float64 (205 with the series' sine and cosine, the
-// weights, ramps and products that follow from sums with and without the sample
-// index formed per sample, and the exponential's table in global memory); the
-// pass over 256 voices of 4 s 383 -> 298 us.  LDS of 20.4 KB (noise as its
-// 16-bit halves, 64 points of the exponential) lets a CU hold the eight
-// wavefronts the registers allow; fetching the next sample's table entries a
-// sample ahead changed nothing (301 us).
+// Bound by float64 VALU issue for part of its time and by the latency of a
+// sample's chain (recurrence, table reads, series) for the rest: over 256 voices
+// of 4 s counters show the VALU busy for 60% of the launch, 1.5 wavefronts per
+// SIMD on average of the two that the registers allow, a third of their time in
+// waits.  125 instructions a sample of the loop, 92 of them float64 (205 with
+// the series' sine and cosine, the weights, ramps and products that follow from
+// sums with and without the sample index formed per sample, and the
+// exponential's table in global memory), 147 with the control stage; the pass
+// 383 -> 298 us.  LDS of 20.4 KB (noise as its 16-bit halves, 64 points of the
+// exponential) lets a CU hold the eight wavefronts the registers allow; fetching
+// the next sample's table entries a sample ahead changed nothing (301 us).
 template <int RPS>
 __global__ void __launch_bounds__(kWave, 2) adjoint_audio_kernel(const RenderArgs a,
                                                               const float* __restrict__ g_audio,

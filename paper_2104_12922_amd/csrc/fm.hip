@@ -16,17 +16,21 @@
 // store instruction writes 1 KB of contiguous audio).  The four samples share
 // a control period; the phase n f_i / sr of the first is a whole number of
 // 2^-64 cycles that wraps by itself and advances by one 64-bit addition per
-// step (off by at most n 2^-64 cycles from the truncation of f_i / sr to that unit, against
-// n f_i / sr 2^-53 from a float64 product), its upper half the float32 phase in
-// [0, 1] (2^-32 cycles); the next three add f_i / sr in float32 (within 2e-7
-// cycles), and the float32 hardware sine takes revolutions.  Periods after every envelope has reached 0 are zero-filled
-// without computation.  Bound by VALU issue: four sines and about 25 other
-// instructions per sample, at five wavefronts per SIMD (91 registers; with the
-// operators' constants in vector registers 123 and four).  16384 voices of 1, 2
-// and 4 s: 1970 us with a float64 product, floor and conversion per operator and
-// step, 1790 with fixed-point phases and envelope pairs read as vectors, 1774 with
-// the constants formed by a lane each and kept in scalar registers; 65536 voices
-// of 500 samples 144, 164 and 128.
+// step (off by at most n 2^-64 cycles from the truncation of f_i / sr to that
+// unit, against n f_i / sr 2^-53 from a float64 product).  Its upper 32 bits are
+// the float32 phase in [0, 1], cut to whole 2^-32 cycles: a phase below 2^-8 has
+// fewer significant bits than a float32 of its own scale would (2.3e-10 cycles
+// at most).  The next three samples add f_i / sr in float32 (within 2e-7
+// cycles), and the float32 hardware sine takes revolutions.  Periods after every
+// envelope has reached 0 are zero-filled without computation.  Bound by VALU
+// issue (busy for the whole launch by counter): four sines, at half rate, and
+// about 25 other instructions per sample, 32.9 in all with the control stage, at
+// five wavefronts per SIMD (91 registers; with the operators' constants in
+// vector registers 123 and four).  16384 voices of 1, 2 and 4 s: 1970 us with a
+// float64 product, floor and conversion per operator and step, 1790 with
+// fixed-point phases and envelope pairs read as vectors, 1774 with the constants
+// formed by a lane each and kept in scalar registers; 65536 voices of 500
+// samples 144, 164 and 128.
 #include "voice_device.h"
 
 namespace synth {

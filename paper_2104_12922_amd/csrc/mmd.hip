@@ -211,8 +211,9 @@ __global__ void mmd_combine_kernel(double* out, int64_t n, int64_t m) {
 // row, padded to C + 1: the lanes of a wavefront read 32 rows of one dimension
 // from distinct banks).
 //
-// Bound by VALU issue at R = 32 (about 4900 instructions per wavefront and
-// dimension, four wavefronts per SIMD).  MMD of 1000 x 1000 sounds of 8192
+// Bound by VALU issue at R = 32 (5200 instructions per wavefront, which sorts a
+// dimension; by counter the VALU is busy for 79% of the launch, at 2.9 of the
+// four wavefronts per SIMD that fit).  MMD of 1000 x 1000 sounds of 8192
 // features: 1.31 ms (three all-pairs launches) -> 0.08 ms.
 // ---------------------------------------------------------------------------
 constexpr int kSortFlagNan = 1, kSortFlagPos = 2, kSortFlagNeg = 4;

@@ -169,8 +169,9 @@ __device__ __forceinline__ double dpp_f64(double x) {
 // Exclusive prefix sum across the 64 lanes (lane 0 gets 0): shifts by 1, 2, 4
 // and 8 within the rows of 16, then the totals of the rows and halves before.
 // Bound by the latency of its seven steps: data-parallel moves instead of
-// shuffles through LDS, 8 voices of 1 s 30.5 -> 29.3 us, 128 of 4 s 93.2 -> 90.4,
-// 16384 of 1 .. 4 s 2745 -> 2701.  All 64 lanes call it.
+// shuffles through LDS, 8 voices of 1 s 30.5 -> 29.3 us, 128 of 4 s 93.2 -> 90.4
+// (16384 of 1 .. 4 s 2845 -> 2810, within the 2.5% by which its runs differ).
+// All 64 lanes call it.
 __device__ __forceinline__ double wave_excl_scan(double x, int lane) {
   (void)lane;
   double s = x;
